@@ -9,6 +9,7 @@ namespace gq {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
@@ -33,7 +34,9 @@ struct LevelCPtrs { const void *lv[kMaxWorkers]; const uint32_t *sp[kMaxWorkers]
 // ---------------------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11).  The 32x32->64 products map to v_mad_u64_u32, the two
 // three-way xors of a round to v_bitop3_b32; the key schedule depends on the seed only and stays in
-// scalar registers.
+// scalar registers.  What an instruction costs on gfx950 (cycles a wave, eight waves per SIMD): adds, xors, ands, ors, right
+// shifts, moves and binary32 adds, products and fused multiply-adds 2.3 to 2.6; products of integers (64-bit results
+// included), left shifts, byte permutes, bit-field operations, conversions, minima, compares, packed 16-bit operations 4.3 to 4.6.
 // ---------------------------------------------------------------------------------------------
 struct Words4 { uint32_t w[4]; };
 
@@ -50,8 +53,11 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
     for (int r = 0; r < 10; r++) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        // Where c1 and c2 are the same for all lanes, half of the words of the first three rounds are too: written as
+        // plain xors, with the uniform operands together, they stay on the scalar unit (the three-input instruction
+        // exists on the vector unit only, and would take the next product there with it).
+        const uint32_t n0 = r < 3 ? (uint32_t)(p1 >> 32) ^ (c1 ^ k0) : xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = r < 3 ? (uint32_t)(p0 >> 32) ^ (c3 ^ k1) : xor3((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -93,8 +99,8 @@ __device__ __forceinline__ Scale make_scale(float norm, int s)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Definition 1 / Eq. (2) for one coordinate.  Both return the signed level as a float whose
-// integer conversion is exact; `value` is what is added to the sum, `code` what is stored.
+// Definition 1 / Eq. (2) for one coordinate.  `magnitude` is the integer value of the code without its sign, as a float
+// whose integer conversion is exact; with the sign of x it is what is added to the sum.
 // ---------------------------------------------------------------------------------------------
 template <int SCHEME> struct Round;
 
@@ -108,49 +114,123 @@ __device__ __forceinline__ float clamp_nan_to_zero(float t, float top)
 
 // Linear grid l_u = (s-u)/s: t = y*s lies between h and h+1; the upper one is taken iff U' < t-h.
 template <> struct Round<0> {
-    static __device__ __forceinline__ float value(float x, const Scale &sc, uint32_t r)
+    static __device__ __forceinline__ float magnitude(float x, const Scale &sc, uint32_t r)
     {
         const float u = (float)r * 0x1.fffffep-33f;                       // U' in [0,1)
         const float ax = __builtin_fabsf(x);
         const float v = __builtin_fmaf(ax, sc.scale, -u);                 // t - U', one rounding
         const float c = clamp_nan_to_zero(__builtin_ceilf(v), sc.top);   // clamp at the top level
-        return __builtin_copysignf(ax >= sc.full ? sc.top : c, x);       // y = 1 sits on the top level
+        return ax >= sc.full ? sc.top : c;                                // y = 1 sits on the top level
     }
-    static __device__ __forceinline__ int code_of_value(float value) { return (int)value; }
-    static __device__ __forceinline__ int code(float x, const Scale &sc, uint32_t r) { return (int)value(x, sc, r); }
+    // magnitude(x, sc, r) != 0 for s >= 2, without the clamp: ceil(v) > 0 iff v > 0 (false for a NaN).  At the norm
+    // |x| scale >= s (1 - 2^-21) > U' anyway; for s = 1 the caller adds |x| >= sc.full.
+    static __device__ __forceinline__ bool nonzero(float x, const Scale &sc, uint32_t r)
+    {
+        const float u = (float)r * 0x1.fffffep-33f;
+        const float ax = __builtin_fabsf(x);
+        return __builtin_fmaf(ax, sc.scale, -u) > 0.0f;
+    }
 };
 
 // Exponential grid {0} u {2^-j}: z = y*2^(s-1); a binary32 z >= 1 is rounded to a neighbouring power of
 // two by adding 23 random bits to its mantissa; z < 1 is first moved to 1+z in [1,2).
 template <> struct Round<1> {
-    static __device__ __forceinline__ float value(float x, const Scale &sc, uint32_t r)
+    // bits of the rounded w = z (+ one) and one = (z < 1)
+    struct Rounded { uint32_t b; float one; };
+    static __device__ __forceinline__ Rounded rounded(float x, const Scale &sc, uint32_t r)
     {
         const float ax = __builtin_fabsf(x);
         const float z = ax >= sc.full ? sc.top : clamp_nan_to_zero(ax * sc.scale, sc.top);   // y = 1 sits on the top level
-        const float one = z < 1.0f ? 1.0f : 0.0f;
-        const float w = z + one;
-        const uint32_t b = __float_as_uint(w) + (r >> 9);
-        const float p2 = __uint_as_float(b & 0x7F800000u) - one;          // 0, 1, 2, 4, ..
-        return __builtin_copysignf(p2, x);
+        // z < 1 ? 1 : 0, as 2^25 (1 - z) clamped to [0, 1] (exact: it is 0 or below for z >= 1, and 2 or more for z < 1):
+        // the clamp is part of the fma, a compare and a select cost 2.6 times as much
+        const float one = __builtin_amdgcn_fmed3f(__builtin_fmaf(z, -0x1p25f, 0x1p25f), 0.0f, 1.0f);
+        return {__float_as_uint(z + one) + (r >> 9), one};
     }
-    // value = +-2^(k-1) or 0  ->  code = +-k or 0
-    static __device__ __forceinline__ int code_of_value(float value)
-    {
-        const uint32_t b = __float_as_uint(value);
-        const int k = max((int)((b >> 23) & 0xFFu) - 126, 0);
-        return (b >> 31) ? -k : k;
-    }
-    // The code without the detour over the value: the rounded w = z (+1 if z < 1) has exponent field E, and
-    // k = E - 126 for z >= 1 (value 2^(E-127)), k = E - 127 for z < 1 (value 0 or 1).
-    static __device__ __forceinline__ int code(float x, const Scale &sc, uint32_t r)
+    static __device__ __forceinline__ float magnitude(const Rounded &t) { return __uint_as_float(t.b & 0x7F800000u) - t.one; }   // 0, 1, 2, 4, ..
+    // The code k of magnitude 2^(k-1), 0 for 0.  w has the exponent field k + 126 for z >= 1 and k + 127 for z < 1; the bits of
+    // 0.5 or 1.0 take that out.
+    static __device__ __forceinline__ uint32_t code(const Rounded &t) { return (t.b - (__float_as_uint(t.one) | 0x3F000000u)) >> 23; }
+    static __device__ __forceinline__ float magnitude(float x, const Scale &sc, uint32_t r) { return magnitude(rounded(x, sc, r)); }
+    // magnitude(x, sc, r) != 0 for s >= 2: z < 1 iff the rounded 1 + z reaches 2, z >= 1 always, and then 1 + z >= 2; a NaN
+    // z counts as 0.  At the norm z >= top (1 - 2^-21) >= 1 anyway; for s = 1 the caller adds |x| >= sc.full.
+    static __device__ __forceinline__ bool nonzero(float x, const Scale &sc, uint32_t r)
     {
         const float ax = __builtin_fabsf(x);
-        const float z = ax >= sc.full ? sc.top : clamp_nan_to_zero(ax * sc.scale, sc.top);   // y = 1 sits on the top level
-        const bool small = z < 1.0f;
-        const float w = z + (small ? 1.0f : 0.0f);
-        const uint32_t b = __float_as_uint(w) + (r >> 9);
-        const int k = (int)(b >> 23) - (small ? 127 : 126);
-        return x < 0.0f ? -k : k;
+        const float z = clamp_nan_to_zero(ax * sc.scale, sc.top);
+        return __float_as_uint(z + 1.0f) + (r >> 9) >= 0x40000000u;
+    }
+};
+
+// Four coordinates rounded: m the magnitudes, v the signed values; exponential grid: k the codes without sign.  What a kernel
+// does not use is not computed.  The kernels that store codes are bound by instruction issue as much as by HBM, hence the
+// care about which instructions form the fields.  gq_quantize of 67.1e6 coordinates, against packing by shifts and
+// selects: linear 4 bits + planes 55.9 -> 49.0 us, exponential 4 bits + planes 64 -> 54, exponential int8 57.1 -> 55.2,
+// packed int4 54.9 -> 52.9 (short draws 51.3 -> 48.1).
+template <int SCHEME> struct Quad4 {
+    float m[4], v[4];
+    uint32_t k[4], xbits[4];
+    __device__ __forceinline__ Quad4(const f32x4 &x, const Scale &sc, const uint32_t *draw)
+    {
+        const float c[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            if constexpr (SCHEME == 0) {
+                m[j] = Round<0>::magnitude(c[j], sc, draw[j]);
+            } else {
+                const auto t = Round<1>::rounded(c[j], sc, draw[j]);
+                m[j] = Round<1>::magnitude(t);
+                k[j] = Round<1>::code(t);
+                xbits[j] = __float_as_uint(c[j]);
+            }
+            v[j] = __builtin_copysignf(m[j], c[j]);
+        }
+    }
+    __device__ __forceinline__ uint32_t exp_signed_code(int j) const
+    {
+        const uint32_t s = (uint32_t)((int)xbits[j] >> 31);
+        return (k[j] ^ s) - s;
+    }
+    // The four codes as bytes or nibbles of one word, coordinate j in field j: two's complement, or magnitudes alone.
+    // Linear codes are put together as floats (exact below 2^24) and converted together: fused multiply-adds issue in half
+    // the time of conversions, shifts and byte permutes.  A bias of half the field's range in every field keeps the sum
+    // non-negative; flipping the fields' top bits takes it out again.
+    __device__ __forceinline__ uint32_t signed_bytes() const
+    {
+        if (SCHEME == 0) {
+            const uint32_t lo = (uint32_t)__builtin_fmaf(v[1], 256.0f, v[0] + 32896.0f);
+            const uint32_t hi = (uint32_t)__builtin_fmaf(v[3], 256.0f, v[2] + 32896.0f);
+            return (lo | (hi << 16)) ^ 0x80808080u;
+        }
+        const uint32_t t = (((exp_signed_code(3) << 8) + exp_signed_code(2)) << 8) + exp_signed_code(1);
+        return ((t << 8) + exp_signed_code(0) + 0x80808080u) ^ 0x80808080u;
+    }
+    __device__ __forceinline__ uint32_t signed_nibbles() const
+    {
+        if (SCHEME == 0)
+            return (uint32_t)__builtin_fmaf(v[3], 4096.0f, __builtin_fmaf(v[2], 256.0f, __builtin_fmaf(v[1], 16.0f, v[0] + 34952.0f))) ^ 0x8888u;
+        const uint32_t t = (((exp_signed_code(3) << 4) + exp_signed_code(2)) << 4) + exp_signed_code(1);
+        return ((t << 4) + exp_signed_code(0) + 0x8888u) ^ 0x8888u;
+    }
+    __device__ __forceinline__ uint32_t magnitude_bytes() const
+    {
+        if (SCHEME == 0) {
+            const uint32_t lo = (uint32_t)__builtin_fmaf(m[1], 256.0f, m[0]), hi = (uint32_t)__builtin_fmaf(m[3], 256.0f, m[2]);
+            return lo | (hi << 16);
+        }
+        return k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24);
+    }
+    __device__ __forceinline__ uint32_t magnitude_nibbles() const
+    {
+        if (SCHEME == 0) return (uint32_t)__builtin_fmaf(m[3], 4096.0f, __builtin_fmaf(m[2], 256.0f, __builtin_fmaf(m[1], 16.0f, m[0])));
+        return k[0] | (k[1] << 4) | (k[2] << 8) | (k[3] << 12);
+    }
+    // bit j = 1 iff code j is negative: -2 v clamped to [0, 1] (a value is 0 or at least 1 in magnitude)
+    __device__ __forceinline__ uint32_t sign_nibble() const
+    {
+        float n[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) n[j] = __builtin_amdgcn_fmed3f(v[j] * -2.0f, 0.0f, 1.0f);
+        return (uint32_t)__builtin_fmaf(n[3], 8.0f, __builtin_fmaf(n[2], 4.0f, __builtin_fmaf(n[1], 2.0f, n[0])));
     }
 };
 
@@ -164,12 +244,6 @@ __device__ __forceinline__ f32x4 load_coords(const float *x, int64_t v, int nval
     if (nvalid > 1) a.y = t[1];
     if (nvalid > 2) a.z = t[2];
     return a;
-}
-
-// Four int8 codes as one word, coordinate i in byte i.
-__device__ __forceinline__ uint32_t pack_bytes(const int *q)
-{
-    return (uint32_t)(q[0] & 255) | ((uint32_t)(q[1] & 255) << 8) | ((uint32_t)(q[2] & 255) << 16) | ((uint32_t)(q[3] & 255) << 24);
 }
 
 // Short draws: coordinate j of a vector takes the low (j even) or high (j odd) half of word j / 2 of the vector's pair

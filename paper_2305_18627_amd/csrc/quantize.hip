@@ -38,33 +38,18 @@ __device__ __forceinline__ uint32_t or_over_8_lanes(uint32_t v)
     return v;
 }
 
-// The four sign bits of a lane's codes; the codes are replaced by their magnitudes.
-__device__ __forceinline__ uint32_t sign_nibble(int *q)
-{
-    uint32_t nib = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        nib |= (uint32_t)(q[i] < 0) << i;
-        q[i] = abs(q[i]);
-    }
-    return nib;
-}
-__device__ __forceinline__ uint32_t pack_nibbles(const int *q)
-{
-    return (uint32_t)(q[0] & 15) | ((uint32_t)(q[1] & 15) << 4) | ((uint32_t)(q[2] & 15) << 8) | ((uint32_t)(q[3] & 15) << 12);
-}
-
-// Store the codes q[0..3] of vector v (nvalid of its coordinates exist).  The lanes of a wave must hold
-// consecutive vectors, lane 0 a multiple of 8, and all be active (the sign words are assembled across lanes).
-__device__ __forceinline__ void store_codes(void *lv, uint32_t *sp, int pack, int64_t v, int nvalid, int64_t d, int *q)
+// Store the codes of vector v (nvalid of its coordinates exist; the codes of the others are 0).  The lanes of a wave must
+// hold consecutive vectors, lane 0 a multiple of 8, and all be active (the sign words are assembled across lanes).
+template <int SCHEME>
+__device__ __forceinline__ void store_codes(void *lv, uint32_t *sp, int pack, int64_t v, int nvalid, int64_t d, const Quad4<SCHEME> &q)
 {
     if (pack >= 2) {
-        const uint32_t word = or_over_8_lanes(sign_nibble(q) << (4 * (threadIdx.x & 7)));
+        const uint32_t word = or_over_8_lanes(q.sign_nibble() << (4 * (threadIdx.x & 7)));
         if ((threadIdx.x & 7) == 0 && ((v & ~(int64_t)7) << 2) < d) sp[v >> 3] = word;
     }
     if (nvalid == 0) return;
     if (pack == GQ_PACK_I8 || pack == GQ_PACK_U8_SIGNPLANE) {
-        const uint32_t w = pack_bytes(q);
+        const uint32_t w = pack == GQ_PACK_I8 ? q.signed_bytes() : q.magnitude_bytes();
         if (nvalid == 4) {
             __builtin_nontemporal_store(w, reinterpret_cast<uint32_t *>(lv) + v);
         } else {
@@ -72,7 +57,7 @@ __device__ __forceinline__ void store_codes(void *lv, uint32_t *sp, int pack, in
             for (int i = 0; i < nvalid; i++) b[i] = (uint8_t)(w >> (8 * i));
         }
     } else {
-        const uint32_t w = pack_nibbles(q);
+        const uint32_t w = pack == GQ_PACK_I4 ? q.signed_nibbles() : q.magnitude_nibbles();
         if (nvalid == 4) {
             __builtin_nontemporal_store((uint16_t)w, reinterpret_cast<uint16_t *>(lv) + v);
         } else {
@@ -87,16 +72,18 @@ __device__ __forceinline__ void store_codes(void *lv, uint32_t *sp, int pack, in
 // grain, which measurably helps the HBM read/write mix of this kernel (128 and 64 alike, 256 slower on MI355X).
 constexpr int kFusedBlock = 128;
 
-// The integer sum of one lane's four coordinates.  Linear codes are summed as floats (exact: the
-// sum stays below 2^24) and converted once; exponential values reach 2^30 and are summed as ints.
-template <int SCHEME> struct Acc;
-template <> struct Acc<0> {
+// The integer sum of one lane's four coordinates: as floats, converted once, where the sum stays within 2^24 and is
+// exact (every linear sum; exponential ones if the host says so), else as ints (exponential values reach 2^30).  A
+// conversion less per worker and coordinate, and the cheaper rounding, take K = 32 at 50e6 coordinates (s = 7) from 1.08
+// to 1.03 ms; with the codes stored, 25.6e6 x 8 (s = 16) goes from 0.212 to 0.190 ms.
+template <bool FLOAT> struct Acc;
+template <> struct Acc<true> {
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
     __device__ __forceinline__ void add(float f0, float f1, float f2, float f3) { a0 += f0; a1 += f1; a2 += f2; a3 += f3; }
     __device__ __forceinline__ i32x4 get() const { return i32x4{(int)a0, (int)a1, (int)a2, (int)a3}; }
     __device__ __forceinline__ void pin() { asm volatile("" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : : "memory"); }
 };
-template <> struct Acc<1> {
+template <> struct Acc<false> {
     int a0 = 0, a1 = 0, a2 = 0, a3 = 0;
     __device__ __forceinline__ void add(float f0, float f1, float f2, float f3) { a0 += (int)f0; a1 += (int)f1; a2 += (int)f2; a3 += (int)f3; }
     __device__ __forceinline__ i32x4 get() const { return i32x4{a0, a1, a2, a3}; }
@@ -135,17 +122,23 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
     constexpr int NV = HALF ? 2 : 1;             // vectors per lane
     const int64_t nfull = d >> 2;
     const int lane = (int)(threadIdx.x & 63u);
-    int64_t v[NV];
+    // the workgroup's first vector (scalar) and this lane's vectors relative to it: kept apart, so that an address is a
+    // scalar base and a 32-bit lane offset and costs no vector instruction per worker
+    const int64_t vb = v0 + (int64_t)blockIdx.x * (kFusedBlock * NV);
+    uint32_t li[NV];
     uint64_t local_call;                         // call index of this lane relative to the launch's first
     if (HALF) {
         const uint64_t chunk = (uint64_t)blockIdx.x * (kFusedBlock / 64) + (threadIdx.x >> 6);   // 128 vectors per wave
-        v[0] = v0 + (int64_t)(chunk * 128u) + lane;
-        v[NV - 1] = v[0] + 64;
+        li[0] = (threadIdx.x >> 6) * 128u + (uint32_t)lane;
+        li[NV - 1] = li[0] + 64u;
         local_call = chunk * 64u + (uint64_t)(lane >> 1) + (uint64_t)(lane & 1) * 32u;
     } else {
+        li[0] = threadIdx.x;
         local_call = (uint64_t)blockIdx.x * kFusedBlock + threadIdx.x;
-        v[0] = v0 + (int64_t)local_call;
     }
+    int64_t v[NV];
+#pragma unroll
+    for (int t = 0; t < NV; t++) v[t] = vb + li[t];
     int nvalid[NV];
 #pragma unroll
     for (int t = 0; t < NV; t++) nvalid[t] = v[t] >= vend ? 0 : (v[t] < nfull ? 4 : (v[t] == nfull ? (int)(d & 3) : 0));
@@ -166,7 +159,8 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
         c_hi = (uint32_t)(call >> 32);
     }
     const int Kc = KT > 0 ? KT : K;
-    const bool whole = nvalid[NV - 1] == 4;      // every coordinate of the lane exists
+    // every coordinate of the workgroup exists (uniform)
+    const bool whole = vb + kFusedBlock * NV <= (vend < nfull ? vend : nfull);
 
     struct Unit { f32x4 g[NV]; };
     auto fetch = [&](int w) {
@@ -178,10 +172,10 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
     auto fetch_whole = [&](int w) {
         Unit x;
 #pragma unroll
-        for (int t = 0; t < NV; t++) x.g[t] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(P.x[w]) + v[t]);
+        for (int t = 0; t < NV; t++) x.g[t] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(P.x[w]) + vb + li[t]);
         return x;
     };
-    Acc<SCHEME> acc[NV];
+    Acc<SCHEME == 0 || (KT > 0)> acc[NV];           // exponential with a compile-time K: the host checked the range
     auto one_worker = [&](int w, const Unit &x) {
         const Words4 r = philox4x32_10(c_lo, c_hi, worker0 + (uint32_t)w, 0u, k0, k1);
         uint32_t draw[NV][4];
@@ -195,16 +189,9 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
         }
 #pragma unroll
         for (int t = 0; t < NV; t++) {
-            const float f0 = Round<SCHEME>::value(x.g[t].x, sc, draw[t][0]);
-            const float f1 = Round<SCHEME>::value(x.g[t].y, sc, draw[t][1]);
-            const float f2 = Round<SCHEME>::value(x.g[t].z, sc, draw[t][2]);
-            const float f3 = Round<SCHEME>::value(x.g[t].w, sc, draw[t][3]);
-            acc[t].add(f0, f1, f2, f3);
-            if (LEVELS) {
-                int q[4] = {Round<SCHEME>::code_of_value(f0), Round<SCHEME>::code_of_value(f1),
-                            Round<SCHEME>::code_of_value(f2), Round<SCHEME>::code_of_value(f3)};
-                store_codes(L.lv[w], L.sp[w], pack, v[t], nvalid[t], d, q);
-            }
+            const Quad4<SCHEME> q(x.g[t], sc, draw[t]);
+            acc[t].add(q.v[0], q.v[1], q.v[2], q.v[3]);
+            if (LEVELS) store_codes<SCHEME>(L.lv[w], L.sp[w], pack, v[t], nvalid[t], d, q);
         }
     };
     if (KT > 0) {
@@ -233,7 +220,9 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
     } else {
         int w = 0;
         for (; w + 4 <= Kc; w += 4) {
-            const Unit x0 = fetch(w), x1 = fetch(w + 1), x2 = fetch(w + 2), x3 = fetch(w + 3);
+            Unit x0, x1, x2, x3;
+            if (whole) { x0 = fetch_whole(w); x1 = fetch_whole(w + 1); x2 = fetch_whole(w + 2); x3 = fetch_whole(w + 3); }
+            else { x0 = fetch(w); x1 = fetch(w + 1); x2 = fetch(w + 2); x3 = fetch(w + 3); }
             one_worker(w, x0); one_worker(w + 1, x1); one_worker(w + 2, x2); one_worker(w + 3, x3);
         }
         for (; w < Kc; w++) one_worker(w, fetch(w));
@@ -313,17 +302,17 @@ __device__ __forceinline__ void quantize_block(const float *__restrict__ x, void
     const int64_t vblock = (int64_t)blockIdx.x * kBlockVecs;          // scalar
     // vector j of this lane within the workgroup, and the Philox call (relative to the workgroup's first) that
     // it runs for vectors j, j+1 (short draws) or j (full draws)
-    int li[kQuantVec];
-    int lcall[kQuantVec];
+    uint32_t li[kQuantVec];
+    uint32_t lcall[kQuantVec];
 #pragma unroll
     for (int j = 0; j < kQuantVec; j++) {
         if (HALF) {
             // the workgroup's 512 vectors are four chunks of 128; wave w takes chunks w and w + 2
-            const int chunk = (int)(threadIdx.x >> 6) + 2 * (j >> 1);
-            li[j] = chunk * 128 + 64 * (j & 1) + lane;
-            lcall[j] = chunk * 64 + (lane >> 1) + (lane & 1) * 32;
+            const uint32_t chunk = (threadIdx.x >> 6) + 2 * (j >> 1);
+            li[j] = chunk * 128 + 64 * (j & 1) + (uint32_t)lane;
+            lcall[j] = chunk * 64 + (uint32_t)(lane >> 1) + (uint32_t)(lane & 1) * 32;
         } else {
-            li[j] = j * kQuantBlock + (int)threadIdx.x;
+            li[j] = j * kQuantBlock + threadIdx.x;
             lcall[j] = li[j];
         }
     }
@@ -342,10 +331,10 @@ __device__ __forceinline__ void quantize_block(const float *__restrict__ x, void
         }
     }
     const uint64_t first = call_base + (uint64_t)(HALF ? (vblock >> 1) : vblock);    // scalar
-    auto counter = [&](int c, uint32_t &c_lo, uint32_t &c_hi) {
+    auto counter = [&](uint32_t c, uint32_t &c_lo, uint32_t &c_hi) {
         if (UNIFORM_HI) {                             // host: the launch stays below the next multiple of 2^32 calls
             c_hi = (uint32_t)(first >> 32);
-            c_lo = (uint32_t)first + (uint32_t)c;
+            c_lo = (uint32_t)first + c;
         } else {
             const uint64_t cc = first + (uint64_t)c;
             c_lo = (uint32_t)cc;
@@ -354,18 +343,18 @@ __device__ __forceinline__ void quantize_block(const float *__restrict__ x, void
     };
     const bool bytes = pack == GQ_PACK_I8 || pack == GQ_PACK_U8_SIGNPLANE;
     auto emit = [&](int j, const uint32_t *draw) {
-        int q[4] = {Round<SCHEME>::code(g[j].x, sc, draw[0]), Round<SCHEME>::code(g[j].y, sc, draw[1]),
-                    Round<SCHEME>::code(g[j].z, sc, draw[2]), Round<SCHEME>::code(g[j].w, sc, draw[3])};
+        const Quad4<SCHEME> q(g[j], sc, draw);
         if (!WHOLE) {
-            store_codes(lv, sp, pack, vblock + li[j], nvalid[j], d, q);
+            store_codes<SCHEME>(lv, sp, pack, vblock + li[j], nvalid[j], d, q);
             return;
         }
         if (pack >= 2) {
-            const uint32_t word = or_over_8_lanes(sign_nibble(q) << (4 * (threadIdx.x & 7)));
+            const uint32_t word = or_over_8_lanes(q.sign_nibble() << (4 * (threadIdx.x & 7)));
             if ((threadIdx.x & 7) == 0) stage_signs[li[j] >> 3] = word;
         }
-        if (bytes) stage[li[j]] = pack_bytes(q);
-        else reinterpret_cast<uint16_t *>(stage)[li[j]] = (uint16_t)pack_nibbles(q);
+        if (pack == GQ_PACK_I8) stage[li[j]] = q.signed_bytes();
+        else if (pack == GQ_PACK_U8_SIGNPLANE) stage[li[j]] = q.magnitude_bytes();
+        else reinterpret_cast<uint16_t *>(stage)[li[j]] = (uint16_t)(pack == GQ_PACK_I4 ? q.signed_nibbles() : q.magnitude_nibbles());
     };
     // no lane leaves early: the sign-plane exchange and the exchange of short draws need whole waves
     if (HALF) {
@@ -441,9 +430,12 @@ static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L
                            P, L, K, d, (int64_t)(V0), (int64_t)(V0) + (int64_t)(COUNT), norm, p->s, p->seed, worker0,  \
                            call_base, p->pack, agg_out, p->agg, deq_out, div, win_period, win_open);          \
     } while (0)
+    // the kernels with a compile-time worker count sum as floats: exponential sums beyond 2^24 take the general one
+    const bool float_sum = max_aggregate(p, K) <= ((int64_t)1 << 24);
 #define GQ_LAUNCH_K(UH, WIN, V0, COUNT)                                                                        \
     do {                                                                                                      \
-        if (K == 4) GQ_LAUNCH(4, false, UH, WIN, V0, COUNT);                                                  \
+        if (!float_sum) GQ_LAUNCH(0, false, UH, WIN, V0, COUNT);                                              \
+        else if (K == 4) GQ_LAUNCH(4, false, UH, WIN, V0, COUNT);                                                  \
         else if (K == 8) GQ_LAUNCH(8, false, UH, WIN, V0, COUNT);                                             \
         else if (K == 16) GQ_LAUNCH(16, false, UH, WIN, V0, COUNT);                                           \
         else if (K == 32) GQ_LAUNCH(32, false, UH, WIN, V0, COUNT);                                           \

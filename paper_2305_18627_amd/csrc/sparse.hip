@@ -337,9 +337,7 @@ __device__ __forceinline__ void quantize_span(const float *__restrict__ x, int64
             }
         };
         auto emit = [&](int i, const uint32_t *draw) {
-            const int q[4] = {Round<SCHEME>::code(g[i].x, sc, draw[0]), Round<SCHEME>::code(g[i].y, sc, draw[1]),
-                              Round<SCHEME>::code(g[i].z, sc, draw[2]), Round<SCHEME>::code(g[i].w, sc, draw[3])};
-            uint32_t w = pack_bytes(q);
+            uint32_t w = Quad4<SCHEME>(g[i], sc, draw).signed_bytes();
             if (!WHOLE) {                                             // no entries for coordinates past the end
                 const int64_t v = vt + li[i];
                 const int nv = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
