@@ -16,30 +16,38 @@ namespace gq {
 // counts the workgroups before it publish; the non-zeros inside a workgroup's span are ranked with wave scans).
 // Receiver side: the K sorted lists are added span by span into the dense int32 sum.
 // =============================================================================================
-constexpr int kCompactBlock = 256;
-constexpr int kCompactTile = kCompactBlock * 16;        // codes per tile: one 128-bit load per thread
-constexpr int kCompactTiles = 8;                        // consecutive tiles per span: 32 KiB of codes
-constexpr int kCompactSpan = kCompactTile * kCompactTiles;
+constexpr int kCompactTile = 4096;                      // codes per entry of the table of tile starts
+constexpr int kWordSpan = 32768;                        // codes per 64-bit word of the scan
+constexpr int kCell = 1024;                             // codes in a row that one wave owns; the granularity of the counts inside a span
+constexpr int kRow = 512;                               // codes whose entries a wave ranks and copies out at a time
+constexpr int kCompactWaves = 8;                        // waves per workgroup
+constexpr int kStage = kCompactWaves * kRow;            // entries that a workgroup can stage
+constexpr int kMaxSpan = kWordSpan;
+
+// A workgroup's span of SPAN codes: cell k of it belongs to wave k mod kCompactWaves.
+template <int SPAN> struct Geometry {
+    static constexpr int kSpanCells = SPAN / kCell;
+    static constexpr int kWaveCells = kSpanCells / kCompactWaves;
+    static constexpr int kPerWord = kWordSpan / SPAN;               // spans that share a 64-bit word of the scan
+    static constexpr int kFieldBits = 64 / kPerWord;
+    typedef typename std::conditional<kPerWord == 1, uint64_t, uint32_t>::type Field;
+    static constexpr Field kPublished = (Field)1 << (kFieldBits - 1);
+    static_assert(kPerWord <= 2 && kWaveCells >= 1, "fields of 32 or 64 bits, at least one cell per wave");
+};
 
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x)    // 0x80 in every byte of x that is not zero
 {
     return (x | ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu)) & 0x80808080u;
 }
 
-// the 16 codes of unit t (bytes 16t .. 16t+15), zeros past the end of the buffer
-__device__ __forceinline__ u32x4 load_code_unit(const uint8_t *lv, int64_t t, int64_t d)
+// the 8 codes of unit t (bytes 8t .. 8t+7), zeros past the end of the buffer
+__device__ __forceinline__ u32x2 load_code_unit(const uint8_t *lv, int64_t t, int64_t d)
 {
-    const int64_t first = t << 4;
-    if (first + 16 <= d) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(lv) + t);
-    uint32_t q[4] = {0u, 0u, 0u, 0u};
-    for (int i = 0; i < 16 && first + i < d; i++) q[i >> 2] |= (uint32_t)lv[first + i] << (8 * (i & 3));
-    return u32x4{q[0], q[1], q[2], q[3]};
-}
-
-__device__ __forceinline__ uint32_t count_unit(const u32x4 &c)
-{
-    return (uint32_t)(__builtin_popcount(nonzero_bytes(c.x)) + __builtin_popcount(nonzero_bytes(c.y)) +
-                      __builtin_popcount(nonzero_bytes(c.z)) + __builtin_popcount(nonzero_bytes(c.w)));
+    const int64_t first = t << 3;
+    if (first + 8 <= d) return __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(lv) + t);
+    uint32_t q[2] = {0u, 0u};
+    for (int i = 0; i < 8 && first + i < d; i++) q[i >> 2] |= (uint32_t)lv[first + i] << (8 * (i & 3));
+    return u32x2{q[0], q[1]};
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -47,13 +55,15 @@ __device__ __forceinline__ uint32_t count_unit(const u32x4 &c)
 // the span from the counts the blocks before it have published, and writes its pairs.  The codes are read once
 // and nothing but the list is written: d + 5 * nnz bytes, the method's own traffic.
 //
-// Spans of kCompactSpan codes are grouped by 64.  One word per span and one word per group (plain stores and loads, no
-// read-modify-write atomics: those serialise chip-wide on one address, measured at about 20 ns each):
-//   span word    bits 31..0 the count of the span, bit 32 set once it is published
-//   group word   bits 39..0 the sum of the counts of the group's 64 spans, bit 40 set once it is published
+// A 64-bit word belongs to every kWordSpan codes; a workgroup's span is all of that or half (span_size), and then
+// two spans share the word, a 32-bit field each.  64 words make a group, which has a word of its own.  Plain stores and
+// loads throughout: read-modify-write atomics on one address serialise chip-wide at about 20 ns each (adding the
+// counts of a group into its word with them makes a call two to five times slower).
+//   span field   the count of the span, top bit set once it is published
+//   group word   bits 39..0 the sum of the counts of the group's spans, bit 40 set once it is published
 // A block publishes its count as soon as it has counted, before it waits for anybody.  What lies before block b
 // is the sum of all earlier groups plus the counts of the earlier blocks of its own group; the last block of a
-// group, which has just added up its 63 predecessors for itself, publishes the group's word.  No block waits for
+// group, which has just added up its predecessors for itself, publishes the group's word.  No block waits for
 // another block's prefix, so the waits do not chain: a few hundred words are read once or twice per block.
 //
 // Why every wait ends.  One workgroup per span.  Workgroups of a one-dimensional grid are handed to the eight XCDs
@@ -65,8 +75,7 @@ __device__ __forceinline__ uint32_t count_unit(const u32x4 &c)
 // (kPrefixMaxPolls polls of about a microsecond): a workgroup that gives up writes nothing and raises count_out to
 // 2^64 - 1, which no real count reaches.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kGroupBlocks = 64;
-constexpr uint64_t kPublished = 1ull << 32;
+constexpr int kGroupWords = 64;
 constexpr uint64_t kGroupPublished = 1ull << 40;
 constexpr int kPrefixMaxPolls = 1 << 21;
 
@@ -85,15 +94,22 @@ __device__ __forceinline__ uint64_t state_load(const uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
+// Inclusive prefix sum over the lanes of a wave: shifts inside the rows of 16, then the last lane of row 0 (2) is added to
+// row 1 (3) and the last lane of row 1 to rows 2 and 3.  Every lane must be active.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, off, 64), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), off, 64);
-        v += ((uint64_t)hi << 32) | lo;
-    }
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);     // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);     // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);     // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);     // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);    // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);    // row_bcast:31 into rows 2 and 3
     return v;
 }
+// the lanes for which c holds (the condition goes straight into a scalar mask)
+__device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
 
 // Number of non-zero codes before span `span`: the counts of the earlier spans of its own group plus the sums of
 // the earlier groups.  Run by one whole wave; the result is uniform.  Both kinds of word are asked for in the same
@@ -103,294 +119,330 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
 // after an unsuccessful poll; the caller counts those.
 struct Before { uint64_t in_group, groups; bool in_group_ready, groups_ready; int64_t next_group; };
 
+template <int SPAN>
 __device__ __forceinline__ void poll_before(const uint64_t *span_words, const uint64_t *group_words, int64_t span, Before *st)
 {
+    constexpr int kPerWord = Geometry<SPAN>::kPerWord;
     const int lane = (int)(threadIdx.x & 63u);
-    const int64_t group = span / kGroupBlocks;
-    const int member = (int)(span - group * kGroupBlocks);
-    uint64_t w_in = kPublished, w_gr = kGroupPublished;
-    if (!st->in_group_ready && lane < member) w_in = state_load(span_words + group * kGroupBlocks + lane);
+    const int64_t group = span / (kGroupWords * kPerWord);
+    const int member = (int)(span - group * (kGroupWords * kPerWord));
+    const int mine = member - lane * kPerWord;               // earlier spans of the group in this lane's word (below 1: none)
+    uint64_t w_in = 0, w_gr = kGroupPublished;
+    if (!st->in_group_ready && mine > 0) w_in = state_load(span_words + group * kGroupWords + lane);
     if (!st->groups_ready && st->next_group + lane < group) w_gr = state_load(group_words + st->next_group + lane);
-    if (!st->in_group_ready && __ballot((w_in & kPublished) == 0) == 0ull) {
-        st->in_group = wave_sum_u64(w_in & 0xFFFFFFFFull);
-        st->in_group_ready = true;
+    if (!st->in_group_ready) {
+        // one field: the flag is the top bit of the upper half, the count the lower half; two: each half has both
+        const uint32_t lo = (uint32_t)w_in, hi = (uint32_t)(w_in >> 32);
+        const bool missing = kPerWord == 1 ? mine > 0 && (hi >> 31) == 0u : (mine > 0 && (lo >> 31) == 0u) || (mine > 1 && (hi >> 31) == 0u);
+        if (ballot(missing) == 0) {
+            const uint32_t sum = kPerWord == 1 ? (mine > 0 ? lo : 0u)
+                                               : (mine > 0 ? lo & 0x7FFFFFFFu : 0u) + (mine > 1 ? hi & 0x7FFFFFFFu : 0u);
+            st->in_group = last_lane(wave_scan(sum));        // at most 2^21
+            st->in_group_ready = true;
+        }
     }
-    if (!st->groups_ready && __ballot((w_gr & kGroupPublished) == 0) == 0ull) {
-        st->groups += wave_sum_u64(w_gr & (kGroupPublished - 1ull));
+    if (!st->groups_ready && ballot(((uint32_t)(w_gr >> 40) & 1u) == 0u) == 0) {
+        st->groups += last_lane(wave_scan((uint32_t)w_gr));  // at most 64 * 2^21
         st->next_group += 64;
         if (st->next_group >= group) st->groups_ready = true;
     }
 }
 
-// Exclusive prefix sums over the block of kCompactTiles counts per thread at once.  Two counts share a 32-bit
-// word (a thread counts at most 16 non-zeros per tile and a tile holds at most 4096, so 16 bits each never
-// carry into each other), which halves the shuffles, and all tiles share the two barriers.
-// rank[j] receives the number of non-zeros of tile j held by the threads before this one, total[j] the tile's count.
-// sh must hold (kCompactBlock / 64) * (kCompactTiles / 2) words.  Every thread must call it.
-__device__ __forceinline__ void block_scan_tiles(const uint32_t *cnt, uint32_t *sh, uint32_t *rank, uint32_t *total)
-{
-    constexpr int kPairs = kCompactTiles / 2, kWaves = kCompactBlock / 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl[kPairs];
-#pragma unroll
-    for (int q = 0; q < kPairs; q++) incl[q] = cnt[2 * q] | (cnt[2 * q + 1] << 16);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-        for (int q = 0; q < kPairs; q++) {
-            const uint32_t t = (uint32_t)__shfl_up((int)incl[q], off, 64);
-            if (lane >= off) incl[q] += t;
-        }
-    }
-    if (lane == 63) {
-#pragma unroll
-        for (int q = 0; q < kPairs; q++) sh[wave * kPairs + q] = incl[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kPairs; q++) {
-        uint32_t before = 0, sum = 0;
-#pragma unroll
-        for (int i = 0; i < kWaves; i++) {
-            const uint32_t w = sh[i * kPairs + q];
-            if (i < wave) before += w;
-            sum += w;
-        }
-        const uint32_t excl = before + incl[q] - (cnt[2 * q] | (cnt[2 * q + 1] << 16));
-        rank[2 * q] = excl & 0xFFFFu;       rank[2 * q + 1] = excl >> 16;
-        total[2 * q] = sum & 0xFFFFu;       total[2 * q + 1] = sum >> 16;
-    }
-    __syncthreads();
-}
+// What the waves of a workgroup share while they turn a span into list entries.
+template <int STAGE> struct SpanShared {
+    uint32_t cells[kMaxSpan / kCell];        // non-zeros in every cell of the span
+    int64_t base;                            // entries before the span
+    uint32_t stage[STAGE];                   // entries: offset in the span << 8 | code
+};
 
-// The list entries of one span, given its codes: c[j] holds the 16 codes of unit threadIdx.x of tile j of the span
-// (zeros past the end of the buffer).  Every thread of the workgroup must call it.
-__device__ __forceinline__ void emit_span(const u32x4 (&c)[kCompactTiles], int64_t d, uint64_t *__restrict__ state, int64_t nspans,
-                                          uint32_t *__restrict__ indices_out, int8_t *__restrict__ values_out, int64_t capacity,
-                                          uint64_t *__restrict__ count_out, uint32_t *__restrict__ tile_starts_out)
+// The list entries of one span.  Wave w holds the codes of cells w, w + kCompactWaves .. of the span, four words per
+// lane and cell: word 4 b + i of lane l holds
+//   W = 2 words in a row per lane   codes 512 (i / 2) + 8 l + 4 (i % 2) .. + 3 of the wave's cell b
+//   W = 1                           codes 256 i + 4 l .. + 3
+// and S.cells holds the counts of the whole span (the caller's barrier has passed).  Every thread must call it.
+//
+// The span's count is published before anything else: it is what the other workgroups wait for.  Finding out what lies
+// before the span takes several round trips to memory (a poll queues behind the bulk reads of the chip), in which
+// the workgroup's slots do nothing (with the wait taken out, 110e6 codes took 23 instead of 37 us).  A span whose entries
+// fit the staging area (one code in four of a short span) is therefore ranked into it before the wait, and every wave but
+// the first ends: the slots go to the next workgroups' reads, and the one wave left copies the entries out.  Denser
+// spans wait with all waves, which then rank and copy out 512 codes at a time, each wave in its own part of the
+// staging area and without a barrier.
+template <int SPAN, int W, int STAGE>
+__device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>::kWaveCells], SpanShared<STAGE> &S, int64_t d,
+                                          uint64_t *__restrict__ state, int64_t nwords, uint32_t *__restrict__ indices_out,
+                                          int8_t *__restrict__ values_out, int64_t capacity, uint64_t *__restrict__ count_out,
+                                          uint32_t *__restrict__ tile_starts_out)
 {
-    __shared__ uint32_t sh[(kCompactBlock / 64) * (kCompactTiles / 2)];
-    __shared__ uint32_t s_idx[kCompactTile];
-    __shared__ int8_t s_val[kCompactTile];
-    __shared__ int64_t s_base;
+    typedef Geometry<SPAN> G;
+    constexpr int kSpanCells = G::kSpanCells, kWaveCells = G::kWaveCells, kGroupSpans = kGroupWords * G::kPerWord;
+    constexpr int kSteps = 2 / W;                            // steps per row of 512 codes
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint64_t *span_words = state + 2;
-    uint64_t *group_words = span_words + nspans;
-    const int64_t span = blockIdx.x;
-    const int64_t t0 = span * (kCompactBlock * kCompactTiles) + threadIdx.x;
-    uint32_t cnt[kCompactTiles], rank[kCompactTiles], total[kCompactTiles];
-#pragma unroll
-    for (int j = 0; j < kCompactTiles; j++) cnt[j] = count_unit(c[j]);
-    block_scan_tiles(cnt, sh, rank, total);
-    uint32_t span_total = 0;
-#pragma unroll
-    for (int j = 0; j < kCompactTiles; j++) span_total += total[j];
-    // the span's count is what the other workgroups wait for: out with it before anything else
-    if (threadIdx.x == 0) __hip_atomic_store(span_words + span, kPublished | span_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t *group_words = span_words + nwords;
+    const int64_t span = blockIdx.x, last_span = (int64_t)gridDim.x - 1;
+    const uint32_t cell_count = lane < kSpanCells ? S.cells[lane] : 0u;
+    const uint32_t cell_start = wave_scan(cell_count) - cell_count;      // entries of the span before cell `lane`
+    const uint32_t span_total = (uint32_t)__builtin_amdgcn_readlane((int)cell_start, kSpanCells);
+    const uint32_t first_index = (uint32_t)(span * SPAN);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(reinterpret_cast<typename G::Field *>(span_words) + span, (typename G::Field)(G::kPublished | span_total), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 
-    // The pairs of a tile are ranked into LDS (a tile never holds more than kCompactTile of them) and then copied
-    // out with consecutive lanes writing consecutive list entries; the list position runs on from tile to tile.
-    // The first tile is ranked while the published count travels; only then does wave 0 ask what lies before.
-    int64_t base = 0;
+    // The entries of row h of the wave's cell b go to stage[r ..]; returns how many there are.
+    auto rank_row = [&](auto bb, auto hh, uint32_t *stage) -> uint32_t {
+        constexpr int b = decltype(bb)::value, h = decltype(hh)::value;
+        uint32_t n = 0;
+        static_for<0, kSteps>([&](auto ss) {
+            constexpr int step = decltype(ss)::value;
+            uint32_t w[W], any = 0, cnt = 0;
 #pragma unroll
-    for (int j = 0; j < kCompactTiles; j++) {
-        if (j > 0 && total[j] == 0) continue;                // uniform over the block: nothing to rank or to copy
-        const int64_t t = t0 + (int64_t)j * kCompactBlock;
-        if (cnt[j] != 0) {
-            uint32_t r = rank[j];
-            const uint32_t w[4] = {c[j].x, c[j].y, c[j].z, c[j].w};
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const uint32_t b = (w[i >> 2] >> (8 * (i & 3))) & 255u;
-                if (b != 0u) {
-                    s_idx[r] = (uint32_t)((t << 4) + i);
-                    s_val[r] = (int8_t)b;
-                    r++;
-                }
+            for (int i = 0; i < W; i++) {
+                w[i] = c[4 * b + 2 * h + (W == 2 ? i : step)];
+                any |= w[i];
             }
-        }
-        if (j == 0) {
-            if (threadIdx.x < 64) {                          // wave 0
-                Before st = {0, 0, false, span / kGroupBlocks == 0, 0};
-                bool group_sum_out = span % kGroupBlocks != kGroupBlocks - 1;     // only a group's last span owes one
-                int polls = 0;
-                bool gave_up = false;
-                for (;;) {
-                    poll_before(span_words, group_words, span, &st);
-                    // the group's last span publishes the group's sum as soon as it has it, before it waits on
-                    if (st.in_group_ready && !group_sum_out) {
-                        if (threadIdx.x == 0)
-                            __hip_atomic_store(group_words + span / kGroupBlocks, kGroupPublished | (st.in_group + span_total),
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        group_sum_out = true;
-                    }
-                    if (st.in_group_ready && st.groups_ready) break;
-                    if (++polls > kPrefixMaxPolls) { gave_up = true; break; }
-                    __builtin_amdgcn_s_sleep(4);
-                }
-                if (threadIdx.x == 0) {
-                    const uint64_t before = st.in_group + st.groups;
-                    if (gave_up) {
-                        atomicMax(reinterpret_cast<unsigned long long *>(count_out), ~0ull);
-                        s_base = -1;
-                    } else {
-                        if (span == nspans - 1)
-                            atomicMax(reinterpret_cast<unsigned long long *>(count_out), (unsigned long long)(before + span_total));
-                        s_base = (int64_t)before;
+            if (ballot(any != 0) == 0) return;          // nothing in the whole wave
+#pragma unroll
+            for (int i = 0; i < W; i++) cnt += (uint32_t)__builtin_popcount(nonzero_bytes(w[i]));
+            const uint32_t incl = wave_scan(cnt);
+            uint32_t r = n + incl - cnt;
+            n += last_lane(incl);
+            // offset in the span of the lane's first code of this step
+            const uint32_t off = (uint32_t)((b * kCompactWaves + wave) * kCell + h * kRow) + (W == 2 ? 8u * lane : 256u * step + 4u * lane);
+#pragma unroll
+            for (int i = 0; i < W; i++) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t q = (w[i] >> (8 * k)) & 255u;
+                    if (q != 0u) {
+                        stage[r] = ((off + 4 * i + k) << 8) | q;
+                        r++;
                     }
                 }
             }
-            __syncthreads();
-            base = s_base;
-            if (base < 0) return;                            // uniform over the block
-            if (tile_starts_out) {
-                // where each tile of the span begins in the list (what the receiver would otherwise search for),
-                // and behind the last tile the end of the list
-                const int64_t ntiles = (d + kCompactTile - 1) / kCompactTile;
-                if (threadIdx.x < kCompactTiles) {
-                    uint32_t start = (uint32_t)base;
-#pragma unroll
-                    for (int jj = 0; jj < kCompactTiles; jj++) if (jj < (int)threadIdx.x) start += total[jj];
-                    const int64_t tile = span * kCompactTiles + threadIdx.x;
-                    if (tile < ntiles) tile_starts_out[tile] = start;
-                }
-                if (span == nspans - 1 && threadIdx.x == 0) tile_starts_out[ntiles] = (uint32_t)(base + span_total);
-            }
-        } else {
-            __syncthreads();
+        });
+        return n;
+    };
+    // n staged entries to list position pos and on, as far as the list reaches
+    auto copy_out = [&](const uint32_t *stage, uint32_t n, int64_t pos) {
+        const int64_t room = capacity - pos;
+        const uint32_t m = room <= 0 ? 0u : room < (int64_t)n ? (uint32_t)room : n;
+        for (uint32_t e = lane; e < m; e += 64) {
+            const uint32_t entry = stage[e];
+            indices_out[pos + e] = first_index + (entry >> 8);
+            values_out[pos + e] = (int8_t)entry;
         }
-        for (uint32_t e = threadIdx.x; e < total[j]; e += kCompactBlock) {
-            if (base + e < capacity) {
-                indices_out[base + e] = s_idx[e];
-                values_out[base + e] = s_val[e];
-            }
-        }
-        base += total[j];
-        __syncthreads();                                     // the staging area is reused by the next tile
+    };
+    const bool staged = span_total <= (uint32_t)STAGE;                  // uniform over the block
+    if (staged) {
+        static_for<0, kWaveCells>([&](auto bb) {
+            constexpr int b = decltype(bb)::value;
+            uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)cell_start, b * kCompactWaves + wave);
+            if (__builtin_amdgcn_readlane((int)cell_count, b * kCompactWaves + wave) == 0) return;
+            at += rank_row(bb, std::integral_constant<int, 0>{}, S.stage + at);
+            rank_row(bb, std::integral_constant<int, 1>{}, S.stage + at);
+        });
+        __syncthreads();
+        if (wave != 0) return;
     }
+    if (wave == 0) {
+        Before st = {0, 0, false, span / kGroupSpans == 0, 0};
+        bool group_sum_out = span % kGroupSpans != kGroupSpans - 1;       // only a group's last span owes one
+        int polls = 0;
+        bool gave_up = false;
+        for (;;) {
+            poll_before<SPAN>(span_words, group_words, span, &st);
+            // the group's last span publishes the group's sum as soon as it has it, before it waits on
+            if (st.in_group_ready && !group_sum_out) {
+                if (lane == 0)
+                    __hip_atomic_store(group_words + span / kGroupSpans, kGroupPublished | (st.in_group + span_total), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                group_sum_out = true;
+            }
+            if (st.in_group_ready && st.groups_ready) break;
+            if (++polls > kPrefixMaxPolls) { gave_up = true; break; }
+            __builtin_amdgcn_s_sleep(4);
+        }
+        const uint64_t before = st.in_group + st.groups;
+        if (lane == 0) {
+            if (gave_up) atomicMax(reinterpret_cast<unsigned long long *>(count_out), ~0ull);
+            else if (span == last_span)
+                atomicMax(reinterpret_cast<unsigned long long *>(count_out), (unsigned long long)(before + span_total));
+            S.base = gave_up ? -1 : (int64_t)before;
+        }
+        if (tile_starts_out && !gave_up) {
+            // where each tile of the span begins in the list (what the receiver would otherwise search for), and behind
+            // the last tile the end of the list
+            const int64_t ntiles = (d + kCompactTile - 1) / kCompactTile;
+            const int64_t tile = span * (SPAN / kCompactTile) + lane / (kCompactTile / kCell);
+            if (lane < kSpanCells && lane % (kCompactTile / kCell) == 0 && tile < ntiles) tile_starts_out[tile] = (uint32_t)before + cell_start;
+            if (span == last_span && lane == 0) tile_starts_out[ntiles] = (uint32_t)before + span_total;
+        }
+        if (staged) {
+            if (!gave_up) copy_out(S.stage, span_total, (int64_t)before);
+            return;
+        }
+    }
+    __syncthreads();
+    const int64_t base = S.base;
+    if (base < 0) return;                                    // uniform over the block
+    uint32_t *stage = S.stage + wave * kRow;
+    static_for<0, kWaveCells>([&](auto bb) {
+        constexpr int b = decltype(bb)::value;
+        int64_t pos = base + (uint32_t)__builtin_amdgcn_readlane((int)cell_start, b * kCompactWaves + wave);
+        static_for<0, 2>([&](auto hh) {
+            const uint32_t n = rank_row(bb, hh, stage);
+            // the wave's own part of the staging area: its reads follow its writes in order
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            copy_out(stage, n, pos);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            pos += n;
+        });
+    });
 }
 
-
-__global__ void __launch_bounds__(kCompactBlock)
-compact_onepass_kernel(const uint8_t *__restrict__ lv, int64_t d, uint64_t *__restrict__ state, int64_t nspans,
+template <int SPAN>
+__global__ void __launch_bounds__(64 * kCompactWaves)
+compact_onepass_kernel(const uint8_t *__restrict__ lv, int64_t d, uint64_t *__restrict__ state, int64_t nwords,
                        uint32_t *__restrict__ indices_out, int8_t *__restrict__ values_out, int64_t capacity,
                        uint64_t *__restrict__ count_out, uint32_t *__restrict__ tile_starts_out)
 {
-    const int64_t t0 = (int64_t)blockIdx.x * (kCompactBlock * kCompactTiles) + threadIdx.x;
-    u32x4 c[kCompactTiles];
+    constexpr int kWaveCells = Geometry<SPAN>::kWaveCells;
+    __shared__ SpanShared<kStage> S;
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t t0 = (int64_t)blockIdx.x * (SPAN / 8) + wave * (kCell / 8) + lane;
+    u32x2 u[2 * kWaveCells];
+    const bool whole = ((int64_t)blockIdx.x + 1) * SPAN <= d;     // uniform over the workgroup
 #pragma unroll
-    for (int j = 0; j < kCompactTiles; j++) c[j] = load_code_unit(lv, t0 + (int64_t)j * kCompactBlock, d);
-    emit_span(c, d, state, nspans, indices_out, values_out, capacity, count_out, tile_starts_out);
+    for (int j = 0; j < 2 * kWaveCells; j++) {
+        const int64_t t = t0 + (j >> 1) * (kCompactWaves * kCell / 8) + (j & 1) * 64;
+        u[j] = whole ? __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(lv) + t) : load_code_unit(lv, t, d);
+    }
+    uint32_t c[4 * kWaveCells];
+#pragma unroll
+    for (int b = 0; b < kWaveCells; b++) {
+        c[4 * b] = u[2 * b].x; c[4 * b + 1] = u[2 * b].y; c[4 * b + 2] = u[2 * b + 1].x; c[4 * b + 3] = u[2 * b + 1].y;
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) cnt += (uint32_t)__builtin_popcount(nonzero_bytes(c[4 * b + i]));
+        const uint32_t sum = last_lane(wave_scan(cnt));
+        if (lane == 0) S.cells[b * kCompactWaves + wave] = sum;
+    }
+    __syncthreads();
+    emit_span<SPAN, 2>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out);
 }
 
 // ---------------------------------------------------------------------------------------------------------
 // Sender side without the dense codes: Algorithm 1's quantisation loop for one worker feeding the list directly.
-// A workgroup quantises its span tile by tile (the same rounding, random stream and call indices as gq_quantize),
-// passes the code words of a tile through LDS so that every thread ends up with 16 consecutive codes, and hands the
-// span to emit_span: 4 d bytes read, 5 nnz written, and the codes never reach memory.
-//   full draws   a thread owns vectors t, t + 256, t + 512, t + 768 of a tile (a wave reads 1 KiB per load)
-//   short draws  a lane owns vectors l and 64 + l of two chunks of 128 vectors and shares its Philox words with its
+// Every wave quantises its own cells of the span, one vector of four coordinates per lane at a time, with the same
+// rounding, random stream and call indices as gq_quantize, and hands the code words to emit_span: 4 d bytes read,
+// 5 nnz written, and the codes never reach memory.
+//   full draws   lane l owns vector l of every 64 consecutive ones
+//   short draws  a lane owns vectors l and 64 + l of 128 consecutive ones and shares its Philox words with its
 //                neighbour lane (one call per eight coordinates, every load contiguous over the wave)
-// The loads of the next tile are issued before the current tile is rounded.
+// The loads of the next cell are issued before the current one is rounded.  A code is non-zero iff
+// Round::nonzero says so, which costs about half of the full rounding rule: where it holds for no coordinate of the
+// wave (most of the time under the (2,2) norm) the codes are not formed at all.
 // ---------------------------------------------------------------------------------------------------------
-template <int SCHEME, bool UNIFORM_HI, bool HALF, bool WHOLE>
-__device__ __forceinline__ void quantize_span(const float *__restrict__ x, int64_t d, const Scale &sc, uint64_t seed, uint32_t worker,
-                                              uint64_t call_base, uint32_t (*stage)[kCompactTile / 4], u32x4 (&c)[kCompactTiles])
+template <int SPAN, int SCHEME, bool UNIFORM_HI, bool HALF, bool WHOLE>
+__device__ __forceinline__ void quantize_cells(const float *__restrict__ x, int64_t d, const Scale &sc, bool one_level, uint64_t seed, uint32_t worker,
+                                                 uint64_t call_base, uint32_t (&c)[4 * Geometry<SPAN>::kWaveCells],
+                                                 uint32_t *cells)
 {
-    constexpr int kTileVecs = kCompactTile / 4;
-    constexpr int kVecs = kTileVecs / kCompactBlock;                  // vectors per thread and tile: 4
+    constexpr int kWaveCells = Geometry<SPAN>::kWaveCells;
+    constexpr int kBatch = kCell / 256;                               // vectors per lane and cell: 4
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const int64_t nfull = d >> 2;
-    const int64_t vspan = (int64_t)blockIdx.x * (kCompactSpan / 4);  // scalar
-    const int t = (int)threadIdx.x;
-    int li[kVecs];
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t v0 = ((int64_t)blockIdx.x * SPAN + wave * kCell) / 4;    // scalar: the wave's first cell
+    constexpr int kNextCell = kCompactWaves * kCell / 4;
+    auto load_batch = [&](int b, f32x4 *g) {
 #pragma unroll
-    for (int i = 0; i < kVecs; i++) {
-        // short draws: a wave takes chunks of 128 consecutive vectors, lane l owns vectors l and 64 + l of a chunk
-        // (see share_short_draws); wave w takes chunks w and w + 4 of the tile's eight
-        const int chunk = (t >> 6) + (kCompactBlock / 64) * (i >> 1);
-        li[i] = HALF ? chunk * 128 + 64 * (i & 1) + (t & 63) : i * kCompactBlock + t;
-    }
-    auto load_tile = [&](int j, f32x4 *g) {
-#pragma unroll
-        for (int i = 0; i < kVecs; i++) {
-            const int64_t v = vspan + (int64_t)j * kTileVecs + li[i];
+        for (int i = 0; i < kBatch; i++) {
+            const int64_t v = v0 + b * kNextCell + i * 64 + lane;
             if (WHOLE) g[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(x) + v);
             else g[i] = load_coords(x, v, v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0));
         }
     };
-    f32x4 g[kVecs], gn[kVecs];
-    load_tile(0, g);
-    static_for<0, kCompactTiles>([&](auto jj) {
-        constexpr int j = decltype(jj)::value;
-        if constexpr (j + 1 < kCompactTiles) load_tile(j + 1, gn);
-        uint32_t *st = stage[j & 1];
-        const int64_t vt = vspan + (int64_t)j * kTileVecs;           // scalar
-        const uint64_t first = call_base + (uint64_t)(HALF ? (vt >> 1) : vt);
-        auto counter = [&](int local, uint32_t &c_lo, uint32_t &c_hi) {
-            if (UNIFORM_HI) {                                         // host: the launch stays below the next multiple of 2^32 calls
-                c_hi = (uint32_t)(first >> 32);
-                c_lo = (uint32_t)first + (uint32_t)local;
-            } else {
-                const uint64_t cc = first + (uint64_t)local;
-                c_lo = (uint32_t)cc;
-                c_hi = (uint32_t)(cc >> 32);
-            }
-        };
-        auto emit = [&](int i, const uint32_t *draw) {
-            uint32_t w = Quad4<SCHEME>(g[i], sc, draw).signed_bytes();
-            if (!WHOLE) {                                             // no entries for coordinates past the end
-                const int64_t v = vt + li[i];
-                const int nv = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
-                if (nv < 4) w &= (1u << (8 * nv)) - 1u;
-            }
-            st[li[i]] = w;
-        };
+    auto counter = [&](uint64_t first, int local, uint32_t &c_lo, uint32_t &c_hi) {
+        if (UNIFORM_HI) {                                             // host: the launch stays below the next multiple of 2^32 calls
+            c_hi = (uint32_t)(first >> 32);
+            c_lo = (uint32_t)first + (uint32_t)local;
+        } else {
+            const uint64_t cc = first + (uint64_t)local;
+            c_lo = (uint32_t)cc;
+            c_hi = (uint32_t)(cc >> 32);
+        }
+    };
+    uint32_t count = 0;                                               // scalar: non-zeros of the current cell
+    // coordinates past the end were loaded as zeros, whose code is 0
+    auto round_vector = [&](const f32x4 &g, const uint32_t *draw) -> uint32_t {
+        uint64_t m0 = ballot(Round<SCHEME>::nonzero(g.x, sc, draw[0])), m1 = ballot(Round<SCHEME>::nonzero(g.y, sc, draw[1]));
+        uint64_t m2 = ballot(Round<SCHEME>::nonzero(g.z, sc, draw[2])), m3 = ballot(Round<SCHEME>::nonzero(g.w, sc, draw[3]));
+        if (one_level) {
+            m0 |= ballot(__builtin_fabsf(g.x) >= sc.full); m1 |= ballot(__builtin_fabsf(g.y) >= sc.full);
+            m2 |= ballot(__builtin_fabsf(g.z) >= sc.full); m3 |= ballot(__builtin_fabsf(g.w) >= sc.full);
+        }
+        uint32_t w = 0;
+        if ((m0 | m1 | m2 | m3) != 0) {
+            count += (uint32_t)(__builtin_popcountll(m0) + __builtin_popcountll(m1) + __builtin_popcountll(m2) + __builtin_popcountll(m3));
+            w = Quad4<SCHEME>(g, sc, draw).signed_bytes();
+        }
+        return w;
+    };
+    f32x4 g[kBatch], gn[kBatch];
+    load_batch(0, g);
+    static_for<0, kWaveCells>([&](auto bb) {
+        constexpr int b = decltype(bb)::value;
+        if constexpr (b + 1 < kWaveCells) load_batch(b + 1, gn);
+        const int64_t vb = v0 + b * kNextCell;                       // scalar
         if (HALF) {
 #pragma unroll
-            for (int h = 0; h < kVecs / 2; h++) {
+            for (int h = 0; h < kBatch / 2; h++) {
                 uint32_t c_lo, c_hi;
-                const int chunk = (t >> 6) + (kCompactBlock / 64) * h, lane = t & 63;
-                counter(chunk * 64 + (lane >> 1) + (lane & 1) * 32, c_lo, c_hi);
+                counter(call_base + (uint64_t)((vb + h * 128) >> 1), (lane >> 1) + (lane & 1) * 32, c_lo, c_hi);
                 const ShortDraws sd = share_short_draws(philox4x32_10(c_lo, c_hi, worker, 0u, k0, k1), (lane & 1) != 0);
                 uint32_t da[4], db[4];
 #pragma unroll
                 for (int i = 0; i < 4; i++) { da[i] = short_draw(sd.a, i); db[i] = short_draw(sd.b, i); }
-                emit(2 * h, da);
-                emit(2 * h + 1, db);
+                c[b * kBatch + 2 * h] = round_vector(g[2 * h], da);
+                c[b * kBatch + 2 * h + 1] = round_vector(g[2 * h + 1], db);
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < kVecs; i++) {
+            for (int i = 0; i < kBatch; i++) {
                 uint32_t c_lo, c_hi;
-                counter(li[i], c_lo, c_hi);
+                counter(call_base + (uint64_t)(vb + i * 64), lane, c_lo, c_hi);
                 const Words4 r = philox4x32_10(c_lo, c_hi, worker, 0u, k0, k1);
-                emit(i, r.w);
+                c[b * kBatch + i] = round_vector(g[i], r.w);
             }
         }
-        __syncthreads();
-        // two staging buffers in turn: the barrier of the next tile separates these reads from the writes of the tile after
-        c[j] = *reinterpret_cast<const u32x4 *>(&st[4 * t]);
-        if constexpr (j + 1 < kCompactTiles) {
+        if (lane == 0) cells[b * kCompactWaves + wave] = count;
+        count = 0;
+        if constexpr (b + 1 < kWaveCells) {
 #pragma unroll
-            for (int i = 0; i < kVecs; i++) g[i] = gn[i];
+            for (int i = 0; i < kBatch; i++) g[i] = gn[i];
         }
     });
 }
 
-template <int SCHEME, bool UNIFORM_HI, bool HALF>
-__global__ void __launch_bounds__(kCompactBlock)
+template <int SPAN, int SCHEME, bool UNIFORM_HI, bool HALF>
+__global__ void __launch_bounds__(64 * kCompactWaves)
 quantize_compact_kernel(const float *__restrict__ x, int64_t d, const float *__restrict__ norm, int s, uint64_t seed, uint32_t worker,
-                        uint64_t call_base, uint64_t *__restrict__ state, int64_t nspans, uint32_t *__restrict__ indices_out,
+                        uint64_t call_base, uint64_t *__restrict__ state, int64_t nwords, uint32_t *__restrict__ indices_out,
                         int8_t *__restrict__ values_out, int64_t capacity, uint64_t *__restrict__ count_out,
                         uint32_t *__restrict__ tile_starts_out)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t stage[2][kCompactTile / 4];
+    __shared__ SpanShared<SPAN == kMaxSpan ? 2 * kStage : kStage> S;
     const Scale sc = make_scale<SCHEME>(*norm, s);
-    const bool whole = ((int64_t)blockIdx.x + 1) * kCompactSpan <= (d & ~(int64_t)3);     // uniform over the workgroup
-    u32x4 c[kCompactTiles];
-    if (whole) quantize_span<SCHEME, UNIFORM_HI, HALF, true>(x, d, sc, seed, worker, call_base, stage, c);
-    else quantize_span<SCHEME, UNIFORM_HI, HALF, false>(x, d, sc, seed, worker, call_base, stage, c);
-    emit_span(c, d, state, nspans, indices_out, values_out, capacity, count_out, tile_starts_out);
+    const bool whole = ((int64_t)blockIdx.x + 1) * SPAN <= (d & ~(int64_t)3);     // uniform over the workgroup
+    uint32_t c[4 * Geometry<SPAN>::kWaveCells];
+    if (whole) quantize_cells<SPAN, SCHEME, UNIFORM_HI, HALF, true>(x, d, sc, s == 1, seed, worker, call_base, c, S.cells);
+    else quantize_cells<SPAN, SCHEME, UNIFORM_HI, HALF, false>(x, d, sc, s == 1, seed, worker, call_base, c, S.cells);
+    __syncthreads();
+    emit_span<SPAN, 1>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out);
 }
 
 struct SparseLists {
@@ -478,6 +530,18 @@ sparse_span_kernel(SparseLists S, int K, int lanes_per_worker, int64_t d, int *_
     }
 }
 
+// words of the scan over 0 <= d <= 2^32 - 1 codes: two spare ones, one per kWordSpan codes, one per group of 64 of those
+static inline int64_t span_words(int64_t d) { return (d + kWordSpan - 1) / kWordSpan; }
+// Codes per workgroup.  Short spans spread a short gradient over the chip and let the workgroups end evenly; long ones pay
+// the wait for the spans before them less often.  Where the lines lie (us a call on MI355X, short / long spans):
+//   gq_compact            25.6e6 codes: 0.2 % non-zeros 13.6 / 13.5, 22 % 19.4 / 21.8;  50e6: 19.6 / 17.5, 31.1 / 32.7;  110e6: 39.2 / 33.8, 61 / 62
+//   gq_quantize_compact   25.6e6: 25.0 / 28.8, 35.3 / 40;  110e6: 0.1 % 86.7 / 85.4, 21 % 110 / 115;  300e6: 225 / 217, 300 / 305
+// (one pass of the earlier kernels, spans of 32768 codes on 256 threads: 16.7, 24.8, 25.8, 38.6, 43.1, 64.6 and 34.2, 41.7, 89.7,
+// 115, 220, 298)
+constexpr int64_t kCompactLongFrom = 1ll << 25, kQuantCompactLongFrom = 1ll << 27;
+static inline int span_size(int64_t d, int64_t long_from) { return d < long_from ? kMaxSpan / 2 : kMaxSpan; }
+static inline int64_t scan_words(int64_t d) { return 2 + span_words(d) + (span_words(d) + kGroupWords - 1) / kGroupWords; }
+
 }  // namespace gq
 
 using namespace gq;
@@ -487,9 +551,7 @@ extern "C" {
 size_t gq_compact_workspace_bytes(int64_t d)
 {
     if (d < 0 || d > 0xFFFFFFFFLL) return 0;
-    const int64_t blocks = (d + kCompactSpan - 1) / kCompactSpan;
-    const int64_t groups = (blocks + kGroupBlocks - 1) / kGroupBlocks;
-    return (size_t)(2 + blocks + groups) * sizeof(uint64_t); // two spare words, a word per block and per group of 64
+    return (size_t)scan_words(d) * sizeof(uint64_t);
 }
 
 int64_t gq_tile_starts_len(int64_t d)
@@ -514,17 +576,20 @@ gq_status gq_compact(const void *levels, int64_t d, const gq_params *p, uint32_t
     if (!aligned(workspace, 8)) return GQ_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)hip_stream;
     uint64_t *state = reinterpret_cast<uint64_t *>(workspace);
-    const int64_t blocks = (d + kCompactSpan - 1) / kCompactSpan;
-    if (!grid_fits(blocks, kCompactBlock)) return GQ_ERR_INVALID_ARG;
+    const int span = span_size(d, kCompactLongFrom);
+    const int64_t blocks = (d + span - 1) / span;
+    if (!grid_fits(blocks, 64 * kCompactWaves)) return GQ_ERR_INVALID_ARG;
     const uint8_t *lv = reinterpret_cast<const uint8_t *>(levels);
     // the scan's words and the count start from zero (a fill kernel, so that the call can be captured in a graph)
-    const int64_t words = 2 + blocks + (blocks + kGroupBlocks - 1) / kGroupBlocks;
+    const int64_t words = scan_words(d);
     hipLaunchKernelGGL(compact_clear_kernel, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, state, words, count_out,
                        blocks == 0 ? tile_starts_out : nullptr);
     if (launched() != GQ_OK) return GQ_ERR_DEVICE;
     if (blocks > 0) {
-        hipLaunchKernelGGL(compact_onepass_kernel, dim3((unsigned)blocks), dim3(kCompactBlock), 0, s, lv, d, state, blocks,
-                           indices_out, values_out, capacity, count_out, tile_starts_out);
+#define GQ_COMPACT(SPAN) hipLaunchKernelGGL(compact_onepass_kernel<SPAN>, dim3((unsigned)blocks), dim3(64 * kCompactWaves), 0, s, lv, d, state, \
+                                            span_words(d), indices_out, values_out, capacity, count_out, tile_starts_out)
+        if (span == kMaxSpan) GQ_COMPACT(kMaxSpan); else GQ_COMPACT(kMaxSpan / 2);
+#undef GQ_COMPACT
         if (launched() != GQ_OK) return GQ_ERR_DEVICE;
     }
     return GQ_OK;
@@ -547,9 +612,10 @@ gq_status gq_quantize_compact(const float *x, int64_t d, const float *norm, cons
     if (!aligned(workspace, 8)) return GQ_ERR_INVALID_ARG;
     hipStream_t hs = (hipStream_t)hip_stream;
     uint64_t *state = reinterpret_cast<uint64_t *>(workspace);
-    const int64_t blocks = (d + kCompactSpan - 1) / kCompactSpan;
-    if (!grid_fits(blocks, kCompactBlock)) return GQ_ERR_INVALID_ARG;
-    const int64_t words = 2 + blocks + (blocks + kGroupBlocks - 1) / kGroupBlocks;
+    const int span = span_size(d, kQuantCompactLongFrom);
+    const int64_t blocks = (d + span - 1) / span;
+    if (!grid_fits(blocks, 64 * kCompactWaves)) return GQ_ERR_INVALID_ARG;
+    const int64_t words = scan_words(d);
     hipLaunchKernelGGL(compact_clear_kernel, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, hs, state, words, count_out,
                        blocks == 0 ? tile_starts_out : nullptr);
     if (launched() != GQ_OK) return GQ_ERR_DEVICE;
@@ -557,15 +623,17 @@ gq_status gq_quantize_compact(const float *x, int64_t d, const float *norm, cons
     const int lane_vecs = half ? 2 : 1;                                  // vectors per Philox call
     const uint64_t call_base = (uint64_t)index_base / (uint64_t)(4 * lane_vecs);
     // the high counter word is a scalar unless the gradient (rounded up to whole spans) crosses 2^32 calls
-    const bool one_stretch = ((call_base & 0xFFFFFFFFull) + (uint64_t)(blocks * (kCompactSpan / 4) / lane_vecs)) <= ((uint64_t)1 << 32);
-#define GQ_QC(SC, UH, HF) hipLaunchKernelGGL((quantize_compact_kernel<SC, UH, HF>), dim3((unsigned)blocks), dim3(kCompactBlock), 0, hs, x, d, \
-                                             norm, p->s, p->seed, worker, call_base, state, blocks, indices_out, values_out, capacity, \
+    const bool one_stretch = ((call_base & 0xFFFFFFFFull) + (uint64_t)(blocks * (span / 4) / lane_vecs)) <= ((uint64_t)1 << 32);
+#define GQ_QC3(SP, SC, UH, HF) hipLaunchKernelGGL((quantize_compact_kernel<SP, SC, UH, HF>), dim3((unsigned)blocks), dim3(64 * kCompactWaves), 0, hs, x, d, \
+                                             norm, p->s, p->seed, worker, call_base, state, span_words(d), indices_out, values_out, capacity, \
                                              count_out, tile_starts_out)
+#define GQ_QC(SC, UH, HF) do { if (span == kMaxSpan) GQ_QC3(kMaxSpan, SC, UH, HF); else GQ_QC3(kMaxSpan / 2, SC, UH, HF); } while (0)
 #define GQ_QC2(SC, UH) do { if (half) GQ_QC(SC, UH, true); else GQ_QC(SC, UH, false); } while (0)
     if (p->scheme == GQ_LINEAR) { if (one_stretch) GQ_QC2(0, true); else GQ_QC2(0, false); }
     else                        { if (one_stretch) GQ_QC2(1, true); else GQ_QC2(1, false); }
 #undef GQ_QC2
 #undef GQ_QC
+#undef GQ_QC3
     return launched();
 }
 

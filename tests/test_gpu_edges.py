@@ -43,3 +43,102 @@ def test_fused_exponential_sums_at_the_float_limit(K, s):
     gq.fused_quantize_aggregate([x.to(DEV) for x in xs], torch.ones(1, device=DEV), p, 0, agg, None, lv)
     assert np.array_equal(host(agg).astype(np.int64), want)
     assert np.array_equal(host(lv[-1]).view(np.int8), O.quantize(xs[-1].numpy(), nf, O.EXP, s, 99, K - 1, 0))
+
+
+def lists_of(lv, d, p, cap=None, starts=True):
+    """gq_compact's list of the int8 codes lv: (indices, values, count, table of tile starts), guard entries behind the list."""
+    cap = d if cap is None else cap
+    idx = torch.full((cap + 8,), -1, dtype=torch.int32, device=DEV)
+    val = torch.full((cap + 8,), 0x5A, dtype=torch.int8, device=DEV)
+    cnt = torch.full((1,), -1, dtype=torch.int64, device=DEV)
+    tab = torch.full((gq.tile_starts_len(d),), -1, dtype=torch.int32, device=DEV)
+    gq.compact(lv, d, p, idx[:cap], val[:cap], cnt, tile_starts_out=tab if starts else None)
+    return idx, val, cnt, tab
+
+
+def check_lists(q, got, cap=None):
+    """A sender's output against the construction: numpy's nonzero and its running counts at the tiles."""
+    idx, val, cnt, tab = (host(t) for t in got)
+    at = np.flatnonzero(q)
+    assert int(cnt[0]) == at.size
+    n = at.size if cap is None else min(at.size, cap)
+    assert np.array_equal(idx[:n].view(np.uint32), at[:n].astype(np.uint32)) and np.array_equal(val[:n], q[at[:n]])
+    assert (idx[n:] == -1).all() and (val[n:] == 0x5A).all()
+    edges = np.minimum(np.arange(tab.size, dtype=np.int64) * 4096, q.size)
+    assert np.array_equal(tab.view(np.uint32), np.searchsorted(at, edges).astype(np.uint32))
+
+
+# A sender's workgroup takes a span of 16384 codes (32768 from 2^25 codes on); up to 4096 entries of a span are staged whole,
+# more go row by row; spans are grouped by 128 (64).
+@pytest.mark.parametrize("d", [16_383, 16_384, 16_385, 32_769, 128 * 16_384, 128 * 16_384 + 1, 129 * 16_384 + 5, 70_001])
+@pytest.mark.parametrize("fill", ["none", "one", "4096", "4097", "last", "all"])
+def test_compact_at_span_and_staging_edges(d, fill):
+    q = np.zeros(d, np.int8)
+    if fill == "one":
+        q[d // 2] = -128
+    elif fill in ("4096", "4097"):                     # so many non-zeros in every span
+        per = np.zeros(16_384, np.int8)
+        per[np.random.default_rng(d).permutation(16_384)[:int(fill)]] = 5
+        q = np.resize(per, d)
+    elif fill == "last":
+        q[-1] = 127
+    elif fill == "all":
+        q = (np.arange(d) % 127 + 1).astype(np.int8)
+    p = gq.make_params(gq.GQ_LINEAR, 127, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=1)
+    lv = torch.from_numpy(q).view(torch.uint8).to(DEV)
+    check_lists(q, lists_of(lv, d, p))
+    if fill in ("4097", "all"):                        # a list that ends inside a span, and one of no entries at all
+        check_lists(q, lists_of(lv, d, p, cap=16_384 + 77), cap=16_384 + 77)
+        check_lists(q, lists_of(lv, d, p, cap=0), cap=0)
+
+
+@pytest.mark.parametrize("d", [(1 << 25) - 1, (1 << 25), (1 << 25) + 32_769])
+@pytest.mark.parametrize("density", [0.001, 0.3])
+def test_compact_either_side_of_the_long_spans(d, density):
+    g = torch.Generator(device=DEV).manual_seed(d)
+    lv = torch.randint(1, 256, (d,), generator=g, device=DEV, dtype=torch.int16).to(torch.uint8)
+    lv[torch.rand(d, generator=g, device=DEV) >= density] = 0
+    p = gq.make_params(gq.GQ_LINEAR, 127, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=1)
+    check_lists(host(lv).view(np.int8), lists_of(lv, d, p))
+
+
+# The list straight from the gradient: one level (s = 1, where the test for a non-zero code has its own case at the norm),
+# densities either side of the staging limit, long spans from 2^27 coordinates on.
+@pytest.mark.parametrize("scheme,s", [("linear", 1), ("exp", 1), ("linear", 127), ("exp", 16)])
+@pytest.mark.parametrize("scale", [1e-6, 0.02, 0.25, 1.0])
+@pytest.mark.parametrize("rng_bits", [32, 16])
+@pytest.mark.parametrize("d", [16_385, 70_003])
+def test_quantize_compact_at_span_and_density_edges(scheme, s, scale, rng_bits, d):
+    g = torch.Generator(device=DEV).manual_seed(d + s)
+    x = torch.randn(d, generator=g, device=DEV).clamp_(-1.0, 1.0).mul_(scale)
+    x[::1001] = 1.0
+    x[7::1001] = -float(np.nextafter(np.float32(1.0), np.float32(0.0)))
+    x[5::4001] = float("nan")
+    x[6::4001] = float("-inf")
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(0 if scheme == "linear" else 1, s, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3, rng_bits=rng_bits)
+    check_quantize_compact_equals_two_calls(x, norm, p)
+    want = O.quantize(host(x), np.float32(1.0), 0 if scheme == "linear" else 1, s, 3, 9, 16, rng_bits)
+    lv = torch.zeros(d, dtype=torch.uint8, device=DEV)
+    gq.quantize(x, norm, p, 9, 16, lv)
+    assert np.array_equal(host(lv).view(np.int8), want)
+
+
+def check_quantize_compact_equals_two_calls(x, norm, p):
+    d = x.numel()
+    lv = torch.empty(d, dtype=torch.uint8, device=DEV)
+    gq.quantize(x, norm, p, 9, 16, lv)
+    want = lists_of(lv, d, p)
+    idx, val = torch.full_like(want[0], -1), torch.full_like(want[1], 0x5A)
+    cnt, tab = torch.full_like(want[2], -1), torch.full_like(want[3], -1)
+    gq.quantize_compact(x, norm, p, 9, 16, idx[:d], val[:d], cnt, tile_starts_out=tab)
+    for a, b in zip((idx, val, cnt, tab), want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("scale", [0.002, 0.3])
+@pytest.mark.parametrize("d", [(1 << 27) - 4, (1 << 27) + 32_771])
+def test_quantize_compact_either_side_of_the_long_spans(d, scale):
+    x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV).mul_(scale).clamp_(-1.0, 1.0)
+    p = gq.make_params(gq.GQ_LINEAR, 7, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3)
+    check_quantize_compact_equals_two_calls(x, torch.ones(1, device=DEV), p)
