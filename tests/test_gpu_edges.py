@@ -142,3 +142,32 @@ def test_quantize_compact_either_side_of_the_long_spans(d, scale):
     x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV).mul_(scale).clamp_(-1.0, 1.0)
     p = gq.make_params(gq.GQ_LINEAR, 7, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3)
     check_quantize_compact_equals_two_calls(x, torch.ones(1, device=DEV), p)
+
+
+# The receiver takes a segment of no more entries than lanes one by one, a longer one four in a row per lane; lists may begin at
+# any element of a buffer (indices 4-byte aligned, values anywhere) and end at the last entry of their capacity.
+@pytest.mark.parametrize("K", [1, 2, 5, 8, 16, 33, 64])
+@pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 31, 33, 63, 64, 65, 511, 513, 514, 515, 2050, 8192])
+@pytest.mark.parametrize("tables", [True, False])
+def test_sparse_aggregate_segment_lengths_and_offsets(K, n, tables):
+    d = 2 * 8192 + 5
+    rng = np.random.default_rng(n * 100 + K)
+    p = gq.make_params(gq.GQ_LINEAR, 127, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=1)
+    want = np.zeros(d, np.int64)
+    idx, val, cnt, tab = [], [], [], []
+    for w in range(K):
+        m = max(1, n - w % 4)                          # per worker and span, ragged between workers
+        at = np.concatenate([np.sort(rng.choice(8192, m, replace=False)), 8192 + np.sort(rng.choice(8192, m, replace=False)), [d - 1]])
+        q = rng.integers(1, 128, at.size) * rng.choice([-1, 1], at.size)
+        want[at] += q
+        off = w % 3                                    # the list ends with its buffer and begins `off` elements in
+        bi = torch.zeros(off + at.size, dtype=torch.int32, device=DEV)
+        bv = torch.zeros(off + at.size, dtype=torch.int8, device=DEV)
+        bi[off:] = torch.from_numpy(at.astype(np.int32)).to(DEV)
+        bv[off:] = torch.from_numpy(q.astype(np.int8)).to(DEV)
+        idx.append(bi[off:]); val.append(bv[off:])
+        cnt.append(torch.tensor([at.size], dtype=torch.int64, device=DEV))
+        tab.append(torch.from_numpy(np.searchsorted(at, np.minimum(np.arange(gq.tile_starts_len(d)) * 4096, d)).astype(np.int32)).to(DEV))
+    agg = torch.full((d,), 77, dtype=torch.int32, device=DEV)
+    gq.sparse_aggregate(idx, val, cnt, d, p, agg, tile_starts=tab if tables else None)
+    assert np.array_equal(host(agg).astype(np.int64), want)
