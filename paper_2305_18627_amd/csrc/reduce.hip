@@ -27,7 +27,11 @@ namespace gq {
 // instruction (exp_reduce_f16_kernel); 8 < s <= 16 on binary32; for s > 16 (32-bit fields) the integer form
 // of the listing is kept.
 // =============================================================================================
-constexpr int kReduceBlock = 128;
+// Four waves share a workgroup's table of leaf values.  Algorithm 2 is bound by instruction issue: scalar bases with 32-bit lane
+// offsets for the loads, unguarded batches in whole workgroups, right instead of left shifts and a quarter of the table
+// set-up per wave take it (s = 7) from 430 to 410 us at K = 32, 50e6 coordinates, from 460 to 388 at K = 64 and from 70 to 62
+// at K = 8, 25e6 each; workgroups of 128 and 64 were 1 to 5 % slower.
+constexpr int kReduceBlock = 256;
 
 // ---- binary32 path ----------------------------------------------------------------------------------------
 // x1, x2: sign * 2^j or 0.  A = (2^s - 1 - r) << (23 - s) for the node's s random bits r.
@@ -120,8 +124,10 @@ exp_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_
         }
         __syncthreads();
     }
-    const int64_t v = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
+    const int64_t block_v = (int64_t)blockIdx.x * kReduceBlock;          // scalar
+    const int64_t v = block_v + threadIdx.x;
     const int64_t nfull = d >> 2;
+    const bool whole = block_v + kReduceBlock <= nfull;                  // uniform: no lane of the block needs a guard
     const int nvalid = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
     if (nvalid == 0) return;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -183,8 +189,14 @@ exp_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_
         // only batches of the second half can be empty; the draws of their inner nodes are needed by nobody else).
         if (2 * w0 < NPAD || w0 < K) {
             uint32_t words[kBatch];
+            if (whole && w0 + kBatch <= K) {
 #pragma unroll
-            for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+                for (int j = 0; j < kBatch; j++)
+                    words[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(Lv.lv[w0 + j]) + block_v + threadIdx.x);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+            }
             static_for<0, kBatch>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
                 constexpr int i = w0 + j;                    // leaf index; the stack depth is popcount(i)
@@ -284,8 +296,10 @@ exp_reduce_f16_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uin
         leaf_value[b] = __builtin_bit_cast(_Float16, bits);
     }
     __syncthreads();
-    const int64_t v = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
+    const int64_t block_v = (int64_t)blockIdx.x * kReduceBlock;          // scalar
+    const int64_t v = block_v + threadIdx.x;
     const int64_t nfull = d >> 2;
+    const bool whole = block_v + kReduceBlock <= nfull;                  // uniform: no lane of the block needs a guard
     const int nvalid = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
     if (nvalid == 0) return;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -324,11 +338,12 @@ exp_reduce_f16_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uin
 #pragma unroll
                 for (int c = 0; c < 4; c++) grp[slot][c] = ~r.w[c] & keep;
             }
-            // byte `node % 4` of the words of coordinates (0,1) resp. (2,3) into the low bytes of the two halves
+            // byte `node % 4` of the words of coordinates (0,1) resp. (2,3) into the high bytes of the two halves, then
+            // down to bits 2..9 (a right shift issues in half the time of a left shift)
             constexpr uint32_t kZero = 0x0Cu;                // v_perm_b32 selector of a zero byte
-            constexpr uint32_t sel = (kZero << 24) | ((uint32_t)(4 + node % PER) << 16) | (kZero << 8) | (uint32_t)(node % PER);
-            const uint32_t A01 = __builtin_amdgcn_perm(grp[slot][1], grp[slot][0], sel) << 2;
-            const uint32_t A23 = __builtin_amdgcn_perm(grp[slot][3], grp[slot][2], sel) << 2;
+            constexpr uint32_t sel = ((uint32_t)(4 + node % PER) << 24) | (kZero << 16) | ((uint32_t)(node % PER) << 8) | kZero;
+            const uint32_t A01 = __builtin_amdgcn_perm(grp[slot][1], grp[slot][0], sel) >> 6;
+            const uint32_t A23 = __builtin_amdgcn_perm(grp[slot][3], grp[slot][2], sel) >> 6;
             st[top - 1][0] = alg2_pair_f16x2(st[top - 1][0], st[top][0], A01);
             st[top - 1][1] = alg2_pair_f16x2(st[top - 1][1], st[top][1], A23);
         }
@@ -339,8 +354,14 @@ exp_reduce_f16_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uin
         // only batches of the second half can be empty; the draws of their inner nodes are needed by nobody else).
         if (2 * w0 < NPAD || w0 < K) {
             uint32_t words[kBatch];
+            if (whole && w0 + kBatch <= K) {
 #pragma unroll
-            for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+                for (int j = 0; j < kBatch; j++)
+                    words[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(Lv.lv[w0 + j]) + block_v + threadIdx.x);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+            }
             static_for<0, kBatch>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
                 constexpr int top0 = __builtin_popcount((unsigned)(w0 + j));     // leaf w0 + j; the stack depth is popcount of it
@@ -412,8 +433,10 @@ avg_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_
                   float *__restrict__ deq_out)
 {
     constexpr int L = NPAD == 1 ? 0 : NPAD == 2 ? 1 : NPAD == 4 ? 2 : NPAD == 8 ? 3 : NPAD == 16 ? 4 : NPAD == 32 ? 5 : 6;
-    const int64_t v = (int64_t)blockIdx.x * kReduceBlock + threadIdx.x;
+    const int64_t block_v = (int64_t)blockIdx.x * kReduceBlock;          // scalar
+    const int64_t v = block_v + threadIdx.x;
     const int64_t nfull = d >> 2;
+    const bool whole = block_v + kReduceBlock <= nfull;                  // uniform: no lane of the block needs a guard
     const int nvalid = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
     if (nvalid == 0) return;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -452,8 +475,16 @@ avg_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_
 #pragma unroll
     for (int w0 = 0; w0 < NPAD; w0 += kBatch) {
         uint32_t words[kBatch];
+        if (whole && w0 + kBatch <= K) {
 #pragma unroll
-        for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+            for (int j = 0; j < kBatch; j++) {
+                if (NIBBLE) words[j] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t *>(Lv.lv[w0 + j]) + block_v + threadIdx.x);
+                else words[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(Lv.lv[w0 + j]) + block_v + threadIdx.x);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kBatch; j++) words[j] = fetch(w0 + j);
+        }
 #pragma unroll
         for (int j = 0; j < kBatch; j++) {
             const int i = w0 + j;

@@ -171,3 +171,24 @@ def test_sparse_aggregate_segment_lengths_and_offsets(K, n, tables):
     agg = torch.full((d,), 77, dtype=torch.int32, device=DEV)
     gq.sparse_aggregate(idx, val, cnt, d, p, agg, tile_starts=tab if tables else None)
     assert np.array_equal(host(agg).astype(np.int64), want)
+
+
+# The tree reductions take workgroups of 1024 coordinates without guards and batches of up to eight workers without checks.
+@pytest.mark.parametrize("d", [1023, 1024, 1025, 2047, 2048, 3 * 1024 + 3])
+@pytest.mark.parametrize("K", [1, 2, 3, 7, 8, 9, 16, 17, 40, 64])
+@pytest.mark.parametrize("kind,s", [("exp", 8), ("exp", 16), ("exp", 17), ("avg8", 127), ("avg4", 7)])
+def test_tree_reductions_at_workgroup_edges(kind, s, K, d):
+    rng = np.random.default_rng(K * 7 + d)
+    qs = [rng.integers(-s, s + 1, d).astype(np.int8) for _ in range(K)]
+    pack = gq.GQ_PACK_I4 if kind == "avg4" else gq.GQ_PACK_I8
+    p = gq.make_params(gq.GQ_EXP if kind == "exp" else gq.GQ_LINEAR, s, pack, gq.GQ_AGG_I32, seed=21)
+    lvs = [torch.from_numpy(O.pack(q, pack)[0]).to(DEV) for q in qs]
+    red = torch.full((gq.levels_nbytes(d, pack) + 8,), 0xAB, dtype=torch.uint8, device=DEV)
+    if kind == "exp":
+        gq.exp_reduce(lvs, d, p, 64, None, red)
+        want = O.exp_tree_reduce(qs, s, 21, 64)
+    else:
+        gq.avg_reduce(lvs, d, p, 64, None, red)
+        want = O.avg_tree_reduce(qs, 21, 64)
+    want = O.pack(np.asarray(want).astype(np.int8), pack)[0]
+    assert np.array_equal(host(red)[:want.size], want) and (host(red)[want.size:] == 0xAB).all()
