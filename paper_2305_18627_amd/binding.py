@@ -1,6 +1,7 @@
 """Thin ctypes binding of the C ABI in include/gqsgd.h.
 
-Argument marshalling only: every step of the path runs in the HIP kernels of libgqsgd.so.
+Argument marshalling only: every step of the path runs in the HIP kernels of libgqsgd.so, and the
+arguments are checked and converted in _marshal.so (csrc/marshal.cpp), which calls the library.
 PyTorch is used for device memory (tensor.data_ptr()) and for the current HIP stream, nothing
 else.  There is no CPU fallback: if the library has not been built, importing this module raises.
 """
@@ -11,6 +12,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libgqsgd.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 
 GQ_MAX_WORKERS = 64
 GQ_OK, GQ_ERR_INVALID_ARG, GQ_ERR_UNSUPPORTED, GQ_ERR_OVERFLOW, GQ_ERR_WORKSPACE, GQ_ERR_DEVICE = range(6)
@@ -41,9 +43,10 @@ class GQError(RuntimeError):
 
 
 def _load():
-    if not os.path.exists(LIB_PATH):
-        raise ImportError("%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
-                          "or python paper_2305_18627_amd/build.py); there is no fallback path" % LIB_PATH)
+    for path in (LIB_PATH, MARSHAL_PATH):
+        if not os.path.exists(path):
+            raise ImportError("%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
+                              "or python paper_2305_18627_amd/build.py); there is no fallback path" % path)
     lib = C.CDLL(LIB_PATH)
     vp, i64, u32, i32, sz = C.c_void_p, C.c_int64, C.c_uint32, C.c_int, C.c_size_t
     pp = C.POINTER(gq_params)
@@ -81,26 +84,22 @@ _lib = None
 _lib = _load()
 
 
+from . import _marshal as _m  # noqa: E402
+
+_m.bind({name: C.cast(getattr(_lib, name), C.c_void_p).value for name in EXPORTS}, torch._C._cuda_getDevice,
+        torch._C._cuda_getCurrentRawStream)
+
+
 def lib():
     """The loaded ctypes library (for tests that call the C ABI directly)."""
     return _lib
 
 
 def _stream(stream):
+    """A stream's address; None stands for the current stream (looked up where the call is made)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
-
-
-def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(None)
-
-
-def _ptr_array(ts):
-    if ts is None:
         return None
-    arr = (C.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
-    return arr
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(st, where):
@@ -108,39 +107,8 @@ def _check(st, where):
         raise GQError(st, where)
 
 
-# The C ABI takes raw pointers and cannot see buffer sizes; the checks below are the binding's part of the
-# contract: a tensor that is too small, not contiguous or not on the GPU is refused here, before any launch.
-def _need(t, nbytes, what):
-    if t is None:
-        return
-    if not t.is_cuda or not t.is_contiguous():
-        raise ValueError("%s must be a contiguous CUDA tensor" % what)
-    have = t.numel() * t.element_size()
-    if have < nbytes:
-        raise ValueError("%s holds %d bytes, the call needs %d" % (what, have, nbytes))
-
-
-def _need_grads(xs):
-    d = xs[0].numel() if xs else 0
-    for x in xs:
-        if x.dtype != torch.float32 or x.numel() != d:
-            raise ValueError("gradients must be float32 tensors of equal length")
-        _need(x, 4 * d, "gradient")
-    return d
-
-
-def _agg_bytes(params):
-    return 2 if params.agg == GQ_AGG_I16 else 4
-
-
-def _need_levels(levels, signplanes, d, params, what="levels"):
-    if levels is None:
-        return
-    for t in levels:
-        _need(t, levels_nbytes(d, params.pack), what)
-    if params.pack >= GQ_PACK_U8_SIGNPLANE and signplanes is not None:
-        for t in signplanes:
-            _need(t, 4 * signplane_nwords(d), "sign plane")
+def _workspace(nbytes, like):
+    return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
 
 
 def make_params(scheme, s, pack=GQ_PACK_I8, agg=GQ_AGG_I32, seed=0, rng_bits=32, flags=0):
@@ -179,56 +147,33 @@ def norm_workspace_bytes(K, d):
 
 def global_norm(xs, kind, norm_out, status_flags=None, workspace=None, stream=None):
     """gq_global_norm over the K tensors xs (fp32, equal length).  Returns the workspace used."""
-    K, d = len(xs), _need_grads(xs)
-    _need(norm_out, 4, "norm_out"); _need(status_flags, 4, "status_flags")
     if workspace is None:
-        workspace = torch.empty(max(norm_workspace_bytes(K, d), 8), dtype=torch.uint8, device=norm_out.device)
-    st = _lib.gq_global_norm(_ptr_array(xs), K, d, int(kind), _ptr(norm_out), _ptr(status_flags),
-                             _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
-    _check(st, "gq_global_norm")
+        workspace = _workspace(max(norm_workspace_bytes(len(xs), xs[0].numel() if len(xs) else 0), 8), norm_out)
+    _check(_m.global_norm(xs, int(kind), norm_out, status_flags, workspace, _stream(stream)), "gq_global_norm")
     return workspace
 
 
 def global_norm_static(xs, kind, norm_out, status_flags=None, stream=None):
     """gq_global_norm_static: the norm with the library's own static scratch; nothing is allocated."""
-    K, d = len(xs), _need_grads(xs)
-    _need(norm_out, 4, "norm_out"); _need(status_flags, 4, "status_flags")
-    st = _lib.gq_global_norm_static(_ptr_array(xs), K, d, int(kind), _ptr(norm_out), _ptr(status_flags), _stream(stream))
-    _check(st, "gq_global_norm_static")
+    _check(_m.global_norm_static(xs, int(kind), norm_out, status_flags, _stream(stream)), "gq_global_norm_static")
 
 
 def quantize(x, norm, params, worker, index_base, levels_out, signplane_out=None, stream=None):
-    d = _need_grads([x])
-    _need(norm, 4, "norm")
-    _need_levels([levels_out], [signplane_out] if signplane_out is not None else None, d, params, "levels_out")
-    st = _lib.gq_quantize(_ptr(x), x.numel(), _ptr(norm), C.byref(params), int(worker), int(index_base),
-                          _ptr(levels_out), _ptr(signplane_out), _stream(stream))
-    _check(st, "gq_quantize")
+    _check(_m.quantize(x, norm, params, int(worker), int(index_base), levels_out, signplane_out, _stream(stream)), "gq_quantize")
 
 
 def int_aggregate(levels, signplanes, d, params, agg_out, stream=None):
-    _need_levels(levels, signplanes, int(d), params)
-    _need(agg_out, _agg_bytes(params) * int(d), "agg_out")
-    st = _lib.gq_int_aggregate(_ptr_array(levels), _ptr_array(signplanes), len(levels), int(d),
-                               C.byref(params), _ptr(agg_out), _stream(stream))
-    _check(st, "gq_int_aggregate")
+    _check(_m.int_aggregate(levels, signplanes, int(d), params, agg_out, _stream(stream)), "gq_int_aggregate")
 
 
 def dequantize(agg, d, norm, params, K, out, stream=None):
-    _need(agg, _agg_bytes(params) * int(d), "agg"); _need(out, 4 * int(d), "out"); _need(norm, 4, "norm")
-    st = _lib.gq_dequantize(_ptr(agg), int(d), _ptr(norm), C.byref(params), int(K), _ptr(out), _stream(stream))
-    _check(st, "gq_dequantize")
+    _check(_m.dequantize(agg, int(d), norm, params, int(K), out, _stream(stream)), "gq_dequantize")
 
 
 def fused_quantize_aggregate(xs, norm, params, index_base=0, agg_out=None, dequant_out=None,
                              levels_out=None, signplanes_out=None, stream=None):
-    K, d = len(xs), _need_grads(xs)
-    _need(norm, 4, "norm"); _need(agg_out, _agg_bytes(params) * d, "agg_out"); _need(dequant_out, 4 * d, "dequant_out")
-    _need_levels(levels_out, signplanes_out, d, params, "levels_out")
-    st = _lib.gq_fused_quantize_aggregate(_ptr_array(xs), K, d, _ptr(norm), C.byref(params), int(index_base),
-                                          _ptr(agg_out), _ptr(dequant_out), _ptr_array(levels_out),
-                                          _ptr_array(signplanes_out), _stream(stream))
-    _check(st, "gq_fused_quantize_aggregate")
+    _check(_m.fused_quantize_aggregate(xs, norm, params, int(index_base), agg_out, dequant_out, levels_out, signplanes_out,
+                                       _stream(stream)), "gq_fused_quantize_aggregate")
 
 
 def bucketed_workspace_bytes(K, d, bucket):
@@ -239,36 +184,19 @@ def bucketed_quantize_aggregate(xs, bucket, kind, params, norms_out, status_flag
                                 workspace=None, stream=None, side_stream=None):
     """gq_bucketed_quantize_aggregate: per bucket its own norm and fused quantize+aggregate; with side_stream the
     norm of the next bucket runs beside the fused call of the current one.  Returns the workspace used."""
-    K, d = len(xs), _need_grads(xs)
-    nb = (d + int(bucket) - 1) // int(bucket) if bucket > 0 else 0
-    _need(norms_out, 4 * nb, "norms_out"); _need(status_flags, 4 * nb, "status_flags")
-    _need(agg_out, _agg_bytes(params) * d, "agg_out"); _need(dequant_out, 4 * d, "dequant_out")
     if workspace is None:
-        workspace = torch.empty(max(bucketed_workspace_bytes(K, d, bucket), 8), dtype=torch.uint8, device=norms_out.device)
-    side = _stream(side_stream) if side_stream is not None else C.c_void_p(None)
-    st = _lib.gq_bucketed_quantize_aggregate(_ptr_array(xs), K, d, int(bucket), int(kind), C.byref(params), _ptr(norms_out),
-                                             _ptr(status_flags), _ptr(agg_out), _ptr(dequant_out), _ptr(workspace),
-                                             workspace.numel() * workspace.element_size(), _stream(stream), side)
-    _check(st, "gq_bucketed_quantize_aggregate")
+        workspace = _workspace(max(bucketed_workspace_bytes(len(xs), xs[0].numel() if len(xs) else 0, bucket), 8), norms_out)
+    _check(_m.bucketed_quantize_aggregate(xs, int(bucket), int(kind), params, norms_out, status_flags, agg_out, dequant_out, workspace,
+                                          _stream(stream), _stream(side_stream) or 0), "gq_bucketed_quantize_aggregate")
     return workspace
 
 
 def exp_reduce(levels, d, params, index_base=0, norm=None, reduced_out=None, dequant_out=None, stream=None):
-    for t in levels:
-        _need(t, int(d), "levels")                               # int8 codes
-    _need(reduced_out, int(d), "reduced_out"); _need(dequant_out, 4 * int(d), "dequant_out"); _need(norm, 4, "norm")
-    st = _lib.gq_exp_reduce(_ptr_array(levels), len(levels), int(d), C.byref(params), int(index_base), _ptr(norm),
-                            _ptr(reduced_out), _ptr(dequant_out), _stream(stream))
-    _check(st, "gq_exp_reduce")
+    _check(_m.exp_reduce(levels, int(d), params, int(index_base), norm, reduced_out, dequant_out, _stream(stream)), "gq_exp_reduce")
 
 
 def avg_reduce(levels, d, params, index_base=0, norm=None, reduced_out=None, dequant_out=None, stream=None):
-    _need_levels(levels, None, int(d), params)
-    _need(reduced_out, levels_nbytes(int(d), params.pack), "reduced_out"); _need(dequant_out, 4 * int(d), "dequant_out")
-    _need(norm, 4, "norm")
-    st = _lib.gq_avg_reduce(_ptr_array(levels), len(levels), int(d), C.byref(params), int(index_base), _ptr(norm),
-                            _ptr(reduced_out), _ptr(dequant_out), _stream(stream))
-    _check(st, "gq_avg_reduce")
+    _check(_m.avg_reduce(levels, int(d), params, int(index_base), norm, reduced_out, dequant_out, _stream(stream)), "gq_avg_reduce")
 
 
 def compact_workspace_bytes(d):
@@ -282,15 +210,10 @@ def tile_starts_len(d):
 def compact(levels, d, params, indices_out, values_out, count_out, workspace=None, stream=None, tile_starts_out=None):
     """gq_compact: the non-zero int8 codes of one worker as (index, code) pairs, and optionally the table of where
     every tile of 4096 coordinates begins in the list.  Returns the workspace used."""
-    _need(levels, int(d), "levels"); _need(count_out, 8, "count_out")
-    _need(values_out, indices_out.numel(), "values_out"); _need(indices_out, 0, "indices_out")
-    _need(tile_starts_out, 4 * tile_starts_len(d), "tile_starts_out")
     if workspace is None:
-        workspace = torch.empty(compact_workspace_bytes(d), dtype=torch.uint8, device=count_out.device)
-    st = _lib.gq_compact(_ptr(levels), int(d), C.byref(params), _ptr(indices_out), _ptr(values_out),
-                         indices_out.numel(), _ptr(count_out), _ptr(tile_starts_out), _ptr(workspace),
-                         workspace.numel() * workspace.element_size(), _stream(stream))
-    _check(st, "gq_compact")
+        workspace = _workspace(compact_workspace_bytes(d), count_out)
+    _check(_m.compact(levels, int(d), params, indices_out, values_out, count_out, workspace, tile_starts_out, _stream(stream)),
+           "gq_compact")
     return workspace
 
 
@@ -298,28 +221,12 @@ def quantize_compact(x, norm, params, worker, index_base, indices_out, values_ou
                      tile_starts_out=None):
     """gq_quantize_compact: the list gq_quantize + gq_compact would write, straight from the gradient.  Returns the
     workspace used."""
-    d = _need_grads([x])
-    _need(norm, 4, "norm"); _need(count_out, 8, "count_out")
-    _need(values_out, indices_out.numel(), "values_out"); _need(indices_out, 0, "indices_out")
-    _need(tile_starts_out, 4 * tile_starts_len(d), "tile_starts_out")
     if workspace is None:
-        workspace = torch.empty(compact_workspace_bytes(d), dtype=torch.uint8, device=count_out.device)
-    st = _lib.gq_quantize_compact(_ptr(x), d, _ptr(norm), C.byref(params), int(worker), int(index_base), _ptr(indices_out),
-                                  _ptr(values_out), indices_out.numel(), _ptr(count_out), _ptr(tile_starts_out), _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _stream(stream))
-    _check(st, "gq_quantize_compact")
+        workspace = _workspace(compact_workspace_bytes(x.numel()), count_out)
+    _check(_m.quantize_compact(x, norm, params, int(worker), int(index_base), indices_out, values_out, count_out, workspace,
+                               tile_starts_out, _stream(stream)), "gq_quantize_compact")
     return workspace
 
 
 def sparse_aggregate(indices, values, counts, d, params, agg_out, stream=None, tile_starts=None):
-    for i, v, c in zip(indices, values, counts):
-        _need(i, 0, "indices"); _need(v, i.numel(), "values"); _need(c, 8, "count")
-    if tile_starts is not None:
-        for t in tile_starts:
-            _need(t, 4 * tile_starts_len(d), "tile_starts")
-    _need(agg_out, 4 * int(d), "agg_out")
-    caps = (C.c_int64 * len(indices))(*[t.numel() for t in indices])
-    starts = None if tile_starts is None else (C.c_void_p * len(tile_starts))(*[t.data_ptr() if t is not None else None for t in tile_starts])
-    st = _lib.gq_sparse_aggregate(_ptr_array(indices), _ptr_array(values), _ptr_array(counts), caps, starts, len(indices),
-                                  int(d), C.byref(params), _ptr(agg_out), _stream(stream))
-    _check(st, "gq_sparse_aggregate")
+    _check(_m.sparse_aggregate(indices, values, counts, int(d), params, agg_out, tile_starts, _stream(stream)), "gq_sparse_aggregate")

@@ -1,4 +1,5 @@
-"""Compile the HIP library for gfx950 into paper_2305_18627_amd/libgqsgd.so (in-tree)."""
+"""Compile the HIP library for gfx950 into paper_2305_18627_amd/libgqsgd.so and the Python binding's argument
+marshalling into _marshal.so beside it (in-tree)."""
 import os
 import subprocess
 
@@ -8,6 +9,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgqsgd.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("common.hip", "norm.hip", "quantize.hip", "aggregate.hip", "reduce.hip",
                                            "sparse.hip", "pipeline.hip")]
+MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 HEADERS = [os.path.join(CSRC, "gq_device.hpp"), os.path.join(CSRC, "gq_host.hpp"),
            os.path.join(ROOT, "include", "gqsgd.h")]
 
@@ -24,10 +27,24 @@ FLAGS = [
 
 
 def is_stale():
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS + [MARSHAL_SOURCE])
+
+
+def _build_marshal(verbose):
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+          "-I", os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", sysconfig.get_paths()["include"],
+          "-o", tmp, MARSHAL_SOURCE, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10"], verbose)
+    os.replace(tmp, MARSHAL)
 
 
 def _run(cmd, verbose):
@@ -37,7 +54,7 @@ def _run(cmd, verbose):
     # hipcc's host pass does not know the packed-fp32 feature and says so; that is harmless
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
     if verbose and out.strip():
         print(out)
 
@@ -52,8 +69,10 @@ def build(force=True, verbose=False):
     os.makedirs(objdir, exist_ok=True)
     objs = [os.path.join(objdir, os.path.basename(src)[:-4] + ".%d.o" % os.getpid()) for src in SOURCES]
     try:
-        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+            marshal = ex.submit(_build_marshal, verbose)
             list(ex.map(lambda so: _run([HIPCC] + FLAGS + ["-c", "-o", so[1], so[0]], verbose), zip(SOURCES, objs)))
+            marshal.result()
         tmp = LIB + ".tmp.%d" % os.getpid()
         _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, verbose)
         os.replace(tmp, LIB)

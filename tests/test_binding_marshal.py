@@ -1,0 +1,67 @@
+"""The binding's native argument marshalling: what it refuses (no GPU needed) and that every form of an argument that it
+accepts reaches the library alike."""
+import pytest
+import torch
+
+import paper_2305_18627_amd as gq
+
+
+def test_refuses_what_is_not_a_fitting_cuda_tensor():
+    p = gq.make_params(gq.GQ_LINEAR, 127)
+    x, n = torch.zeros(8), torch.zeros(1)
+    for call in (lambda: gq.global_norm([x], 0, n), lambda: gq.global_norm_static((x,), 0, n), lambda: gq.quantize(x, n, p, 0, 0, x),
+                 lambda: gq.int_aggregate([x], None, 8, p, x), lambda: gq.dequantize(x, 8, n, p, 1, x),
+                 lambda: gq.fused_quantize_aggregate([x], n, p, 0, x), lambda: gq.exp_reduce([x], 8, p, 0, n, x),
+                 lambda: gq.avg_reduce([x], 8, p, 0, n, x), lambda: gq.compact(x, 8, p, x, x, n),
+                 lambda: gq.quantize_compact(x, n, p, 0, 0, x, x, n), lambda: gq.sparse_aggregate([x], [x], [n], 8, p, x),
+                 lambda: gq.bucketed_quantize_aggregate([x], 8, 0, p, n, None, x)):
+        with pytest.raises(ValueError):
+            call()
+    for bad in (None, 3, "x", [x], [None]):
+        with pytest.raises((TypeError, ValueError, AttributeError)):
+            gq.quantize(bad, n, p, 0, 0, x)
+        with pytest.raises((TypeError, ValueError, AttributeError)):
+            gq.global_norm_static([bad], 0, n)
+    with pytest.raises(TypeError):
+        gq.dequantize(x, 8, n, b"not params", 1, x)
+
+
+@pytest.mark.gpu
+def test_sequences_streams_and_optional_arguments_reach_the_library_alike():
+    dev = torch.device("cuda:0")
+    K, d = 3, 5003
+    both = torch.randn(K, 5008, device=dev)
+    rows = [both[i, :d] for i in range(K)]
+    ref = None
+    side = torch.cuda.Stream()
+    p = gq.make_params(gq.GQ_LINEAR, 127, seed=4)
+    for xs in (rows, tuple(rows), both[:, :5004].contiguous()[:, :d].contiguous()):
+        if isinstance(xs, torch.Tensor):               # rows of one tensor, kept 16-byte aligned
+            xs = both[:, :5008]
+        for stream in (None, torch.cuda.current_stream(), torch.cuda.current_stream().cuda_stream, side, side.cuda_stream):
+            side.wait_stream(torch.cuda.current_stream())
+            n = xs[0].numel()
+            norm, flags = torch.zeros(1, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
+            agg, mean = torch.zeros(n, dtype=torch.int32, device=dev), torch.zeros(n, device=dev)
+            torch.cuda.synchronize()
+            ws = gq.global_norm(xs, gq.GQ_NORM_LINF, norm, flags, stream=stream)
+            assert ws.numel() >= gq.norm_workspace_bytes(K, n)
+            gq.fused_quantize_aggregate(xs, norm, p, 0, agg, mean, stream=stream)
+            torch.cuda.synchronize()
+            got = (norm, flags, agg[:d], mean[:d])
+            if n == d:
+                ref = ref or got
+                assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    with torch.cuda.stream(side):                      # None is the stream that is current where the call is made
+        norm2 = torch.zeros(1, device=dev)
+        gq.global_norm_static(rows, gq.GQ_NORM_LINF, norm2)
+        done = torch.cuda.Event()
+        done.record(side)
+    done.synchronize()
+    assert torch.equal(norm2, ref[0])
+    with pytest.raises(ValueError):
+        gq.fused_quantize_aggregate(rows, norm, p, 0, agg, None, [torch.zeros(d, dtype=torch.uint8, device=dev)] * 2)
+    with pytest.raises(gq.GQError):
+        gq.global_norm([both[0, :d]] * 65, gq.GQ_NORM_LINF, norm)
+    with pytest.raises(ValueError):
+        gq.global_norm(both.t()[:K], gq.GQ_NORM_LINF, norm)
