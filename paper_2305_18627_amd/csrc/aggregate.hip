@@ -17,9 +17,21 @@ namespace gq {
 // =============================================================================================
 constexpr int kAggBlock = 128;
 
+// the pointers that a format has
+template <int PACK> using CodesOf = typename std::conditional<(PACK >= GQ_PACK_U8_SIGNPLANE), LevelCPtrs, CodePtrs>::type;
+template <int PACK> static inline CodesOf<PACK> codes_of_format(const LevelCPtrs &L)
+{
+    if constexpr (PACK >= GQ_PACK_U8_SIGNPLANE) return L;
+    else {
+        CodePtrs r;
+        for (int i = 0; i < kMaxWorkers; i++) r.lv[i] = L.lv[i];
+        return r;
+    }
+}
+
 template <int SCHEME, int PACK>
 __global__ void __launch_bounds__(kAggBlock)
-int_aggregate_kernel(LevelCPtrs L, int K, int64_t d, int64_t v_begin, void *__restrict__ agg_out, int agg_fmt)
+int_aggregate_kernel(CodesOf<PACK> L, int K, int64_t d, int64_t v_begin, void *__restrict__ agg_out, int agg_fmt)
 {
     constexpr bool kNibble = (PACK == GQ_PACK_I4 || PACK == GQ_PACK_U4_SIGNPLANE);
     constexpr bool kPlane = (PACK == GQ_PACK_U8_SIGNPLANE || PACK == GQ_PACK_U4_SIGNPLANE);
@@ -67,7 +79,8 @@ int_aggregate_kernel(LevelCPtrs L, int K, int64_t d, int64_t v_begin, void *__re
                 if (nvalid == 3) t.codes |= (uint32_t)b[1] << 8;
             }
         }
-        t.signs = kPlane ? (L.sp[w][v >> 3] >> (4 * (int)(v & 7))) & 15u : 0u;
+        t.signs = 0u;
+        if constexpr (kPlane) t.signs = (L.sp[w][v >> 3] >> (4 * (int)(v & 7))) & 15u;
         return t;
     };
     int a0 = 0, a1 = 0, a2 = 0, a3 = 0;
@@ -150,7 +163,7 @@ constexpr int kNibCoords = 8;
 
 template <int SCHEME, bool PLANE>
 __global__ void __launch_bounds__(kNibBlock)
-int_aggregate_nibble_kernel(LevelCPtrs L, int K, void *__restrict__ agg_out, int agg_fmt)
+int_aggregate_nibble_kernel(CodesOf<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4> L, int K, void *__restrict__ agg_out, int agg_fmt)
 {
     static_assert(!(SCHEME == 1 && PLANE), "exponential sign-plane values do not fit 16-bit halves");
     constexpr int kEntries = PLANE ? 1024 : 256;
@@ -192,7 +205,10 @@ int_aggregate_nibble_kernel(LevelCPtrs L, int K, void *__restrict__ agg_out, int
         }
     };
     auto codes_of = [&](int w) { return __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(L.lv[w]) + u); };
-    auto signs_of = [&](int w) { return PLANE ? (uint32_t)reinterpret_cast<const uint8_t *>(L.sp[w])[u] : 0u; };
+    auto signs_of = [&](int w) -> uint32_t {
+        if constexpr (PLANE) return reinterpret_cast<const uint8_t *>(L.sp[w])[u];
+        else return 0u;
+    };
     int w = 0;
     for (; w + 8 <= K; w += 8) {                     // eight workers' loads are issued before the first is consumed
         uint32_t c[8], sb[8];
@@ -297,8 +313,8 @@ gq_status gq_int_aggregate(const void *const *levels, const uint32_t *const *sig
         if (wide_blocks > 0) {
             const dim3 wgrid((unsigned)wide_blocks), wblock(kNibBlock);
             if (p->pack == GQ_PACK_U4_SIGNPLANE) hipLaunchKernelGGL((int_aggregate_nibble_kernel<0, true>), wgrid, wblock, 0, s, L, K, agg_out, p->agg);
-            else if (p->scheme == GQ_LINEAR) hipLaunchKernelGGL((int_aggregate_nibble_kernel<0, false>), wgrid, wblock, 0, s, L, K, agg_out, p->agg);
-            else hipLaunchKernelGGL((int_aggregate_nibble_kernel<1, false>), wgrid, wblock, 0, s, L, K, agg_out, p->agg);
+            else if (p->scheme == GQ_LINEAR) hipLaunchKernelGGL((int_aggregate_nibble_kernel<0, false>), wgrid, wblock, 0, s, codes_of_format<GQ_PACK_I4>(L), K, agg_out, p->agg);
+            else hipLaunchKernelGGL((int_aggregate_nibble_kernel<1, false>), wgrid, wblock, 0, s, codes_of_format<GQ_PACK_I4>(L), K, agg_out, p->agg);
             if (launched() != GQ_OK) return GQ_ERR_DEVICE;
             v_begin = wide_blocks * (kNibBlock * kNibCoords / 4);
             if (v_begin >= nvec) return GQ_OK;
@@ -307,7 +323,7 @@ gq_status gq_int_aggregate(const void *const *levels, const uint32_t *const *sig
     const int64_t blocks = (nvec - v_begin + kAggBlock - 1) / kAggBlock;
     if (!grid_fits(blocks, kAggBlock)) return GQ_ERR_INVALID_ARG;
     const dim3 grid((unsigned)blocks), block(kAggBlock);
-#define GQ_AGG(SC, PK) hipLaunchKernelGGL((int_aggregate_kernel<SC, PK>), grid, block, 0, s, L, K, d, v_begin, agg_out, p->agg)
+#define GQ_AGG(SC, PK) hipLaunchKernelGGL((int_aggregate_kernel<SC, PK>), grid, block, 0, s, codes_of_format<PK>(L), K, d, v_begin, agg_out, p->agg)
     if (p->scheme == GQ_LINEAR) {
         switch (p->pack) {
         case GQ_PACK_I8: GQ_AGG(0, GQ_PACK_I8); break;

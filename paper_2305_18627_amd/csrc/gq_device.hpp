@@ -26,10 +26,21 @@ template <int BEGIN, int END, typename F> __device__ __forceinline__ void static
 }
 constexpr int kMaxWorkers = 64;
 
-// Per-worker device pointers, passed to the kernels by value.
-struct GradPtrs { const float *x[kMaxWorkers]; };
+// Per-worker device pointers, passed to the kernels by value.  A kernel takes no more of them than it can use: launching
+// one with 1.5 KB of arguments costs the host 1.4 us more than one with a few words (5.1 against 3.7 us).
+template <int N> struct GradPtrsN { const float *x[N]; };
+typedef GradPtrsN<kMaxWorkers> GradPtrs;
+template <int KT> using GradPtrsFor = GradPtrsN<(KT > 0 ? KT : kMaxWorkers)>;       // KT: compile-time worker count, 0 = run-time
+template <int KT> static inline GradPtrsFor<KT> pointers_for(const GradPtrs &P)
+{
+    GradPtrsFor<KT> r;
+    for (int i = 0; i < (KT > 0 ? KT : kMaxWorkers); i++) r.x[i] = P.x[i];
+    return r;
+}
 struct LevelPtrs { void *lv[kMaxWorkers]; uint32_t *sp[kMaxWorkers]; };
 struct LevelCPtrs { const void *lv[kMaxWorkers]; const uint32_t *sp[kMaxWorkers]; };
+struct CodePtrs { const void *lv[kMaxWorkers]; };                                    // codes without sign planes
+struct NoPtrs {};
 
 // ---------------------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11).  The 32x32->64 products map to v_mad_u64_u32, the two

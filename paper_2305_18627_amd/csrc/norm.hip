@@ -87,7 +87,7 @@ template <bool MAXNORM> struct NormAcc {
 
 template <bool MAXNORM, int KT>
 __global__ void __launch_bounds__(kNormTileBlock)
-norm_tile_kernel(GradPtrs P, int K, int64_t d, int64_t tiles_per_block, uint64_t *__restrict__ partial)
+norm_tile_kernel(GradPtrsFor<KT> P, int K, int64_t d, int64_t tiles_per_block, uint64_t *__restrict__ partial)
 {
     const int64_t nvec = d >> 2;
     const int Kc = KT > 0 ? KT : K;
@@ -225,7 +225,7 @@ static gq_status launch_global_norm(const GradPtrs &P, int K, int64_t d, gq_norm
         int64_t blocks, tpb;
         norm_tile_shape(d, &blocks, &tpb);
         const dim3 grid((unsigned)blocks), block(kNormTileBlock);
-#define GQ_NORM(MX, KT) hipLaunchKernelGGL((norm_tile_kernel<MX, KT>), grid, block, 0, st, P, K, d, tpb, partial)
+#define GQ_NORM(MX, KT) hipLaunchKernelGGL((norm_tile_kernel<MX, KT>), grid, block, 0, st, pointers_for<KT>(P), K, d, tpb, partial)
         if (kind == GQ_NORM_LINF) {
             if (K == 16) GQ_NORM(true, 16); else if (K == 8) GQ_NORM(true, 8); else if (K == 32) GQ_NORM(true, 32);
             else if (K == 4) GQ_NORM(true, 4); else GQ_NORM(true, 0);

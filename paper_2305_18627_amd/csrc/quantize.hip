@@ -114,7 +114,7 @@ constexpr int kWindowMaxPolls = 1024;             // polls of about 0.2 us each:
 // workers and leave the vector ALU.
 template <int SCHEME, int KT, bool LEVELS, bool UNIFORM_HI, bool WINDOWS, bool HALF>
 __global__ void __launch_bounds__(kFusedBlock)
-quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0, int64_t vend, const float *__restrict__ norm, int s,
+quantize_aggregate_kernel(GradPtrsFor<KT> P, typename std::conditional<LEVELS, LevelPtrs, NoPtrs>::type L, int K, int64_t d, int64_t v0, int64_t vend, const float *__restrict__ norm, int s,
                           uint64_t seed, uint32_t worker0, uint64_t call_base, int pack,
                           void *__restrict__ agg_out, int agg_fmt, float *__restrict__ deq_out, float deq_div,
                           uint32_t win_period, uint32_t win_open)
@@ -191,7 +191,7 @@ quantize_aggregate_kernel(GradPtrs P, LevelPtrs L, int K, int64_t d, int64_t v0,
         for (int t = 0; t < NV; t++) {
             const Quad4<SCHEME> q(x.g[t], sc, draw[t]);
             acc[t].add(q.v[0], q.v[1], q.v[2], q.v[3]);
-            if (LEVELS) store_codes<SCHEME>(L.lv[w], L.sp[w], pack, v[t], nvalid[t], d, q);
+            if constexpr (LEVELS) store_codes<SCHEME>(L.lv[w], L.sp[w], pack, v[t], nvalid[t], d, q);
         }
     };
     if (KT > 0) {
@@ -405,6 +405,12 @@ quantize_kernel(const float *__restrict__ x, void *__restrict__ lv, uint32_t *__
     else quantize_block<SCHEME, UNIFORM_HI, HALF, false>(x, lv, sp, d, sc, seed, worker, call_base, pack, stage, stage_signs);
 }
 
+template <bool LEVELS> static inline typename std::conditional<LEVELS, const LevelPtrs &, NoPtrs>::type level_ptrs(const LevelPtrs &L)
+{
+    if constexpr (LEVELS) return L;
+    else return NoPtrs{};
+}
+
 template <int SCHEME, bool HALF>
 static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L, bool levels, int K, int64_t d,
                                            const float *norm, const gq_params *p, uint32_t worker0,
@@ -427,7 +433,7 @@ static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L
         const int64_t blocks_ = ((COUNT) + kFusedBlock * kLaneVecs - 1) / (kFusedBlock * kLaneVecs);          \
         if (!grid_fits(blocks_, kFusedBlock)) return GQ_ERR_INVALID_ARG;                                                   \
         hipLaunchKernelGGL((quantize_aggregate_kernel<SCHEME, KT, LV, UH, WIN, HALF>), dim3((unsigned)blocks_), block, 0, st, \
-                           P, L, K, d, (int64_t)(V0), (int64_t)(V0) + (int64_t)(COUNT), norm, p->s, p->seed, worker0,  \
+                           pointers_for<KT>(P), level_ptrs<LV>(L), K, d, (int64_t)(V0), (int64_t)(V0) + (int64_t)(COUNT), norm, p->s, p->seed, worker0,  \
                            call_base, p->pack, agg_out, p->agg, deq_out, div, win_period, win_open);          \
     } while (0)
     // the kernels with a compile-time worker count sum as floats: exponential sums beyond 2^24 take the general one
@@ -536,9 +542,8 @@ gq_status gq_fused_quantize_aggregate(const float *const *x, int K, int64_t d, c
     for (int i = 0; i < K; i++) {
         if (d > 0 && !aligned(x[i], 16)) return GQ_ERR_INVALID_ARG;
         P.x[i] = x[i];
-        L.lv[i] = nullptr;
-        L.sp[i] = nullptr;
         if (levels) {
+            L.sp[i] = nullptr;
             if (d > 0 && !aligned(levels_out[i], 16)) return GQ_ERR_INVALID_ARG;
             L.lv[i] = levels_out[i];
             if (plane) {

@@ -108,7 +108,7 @@ template <int W0, int J> using jj_leaf = std::integral_constant<int, W0 + J>;
 
 template <int NPAD, bool UNIFORM_HI, int W>
 __global__ void __launch_bounds__(kReduceBlock)
-exp_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_t call_base,
+exp_reduce_kernel(CodePtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_t call_base,
                   const float *__restrict__ norm, void *__restrict__ reduced_out, float *__restrict__ deq_out)
 {
     constexpr int L = NPAD == 1 ? 0 : NPAD == 2 ? 1 : NPAD == 4 ? 2 : NPAD == 8 ? 3 : NPAD == 16 ? 4 : NPAD == 32 ? 5 : 6;
@@ -283,7 +283,7 @@ exp_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_
 // register, which halves the instructions of the pair reductions (they dominate the kernel's time).
 template <int NPAD, bool UNIFORM_HI>
 __global__ void __launch_bounds__(kReduceBlock)
-exp_reduce_f16_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_t call_base,
+exp_reduce_f16_kernel(CodePtrs Lv, int K, int64_t d, int s, uint64_t seed, uint64_t call_base,
                       const float *__restrict__ norm, void *__restrict__ reduced_out, float *__restrict__ deq_out)
 {
     constexpr int L = NPAD == 1 ? 0 : NPAD == 2 ? 1 : NPAD == 4 ? 2 : NPAD == 8 ? 3 : NPAD == 16 ? 4 : NPAD == 32 ? 5 : 6;
@@ -428,7 +428,7 @@ exp_reduce_f16_kernel(LevelCPtrs Lv, int K, int64_t d, int s, uint64_t seed, uin
 // =============================================================================================
 template <int NPAD, bool NIBBLE, bool UNIFORM_HI>
 __global__ void __launch_bounds__(kReduceBlock)
-avg_reduce_kernel(LevelCPtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_base,
+avg_reduce_kernel(CodePtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_base,
                   const float *__restrict__ norm, float deq_div, void *__restrict__ reduced_out,
                   float *__restrict__ deq_out)
 {
@@ -557,11 +557,10 @@ gq_status gq_exp_reduce(const void *const *levels, int K, int64_t d, const gq_pa
     if (!levels || K < 1 || K > GQ_MAX_WORKERS || d < 0 || index_base < 0 || (index_base & 3) != 0) return GQ_ERR_INVALID_ARG;
     if (!reduced_out && !dequant_out) return GQ_ERR_INVALID_ARG;
     if (dequant_out && !aligned(norm, 4)) return GQ_ERR_INVALID_ARG;
-    LevelCPtrs Lv;
+    CodePtrs Lv;
     for (int i = 0; i < K; i++) {
         if (d > 0 && !aligned(levels[i], 16)) return GQ_ERR_INVALID_ARG;
         Lv.lv[i] = levels[i];
-        Lv.sp[i] = nullptr;
     }
     if (d > 0 && ((reduced_out && !aligned(reduced_out, 16)) || (dequant_out && !aligned(dequant_out, 16)))) return GQ_ERR_INVALID_ARG;
     if (d == 0) return GQ_OK;
@@ -607,11 +606,10 @@ gq_status gq_avg_reduce(const void *const *levels, int K, int64_t d, const gq_pa
     if (!levels || K < 1 || K > GQ_MAX_WORKERS || d < 0 || index_base < 0 || (index_base & 3) != 0) return GQ_ERR_INVALID_ARG;
     if (!reduced_out && !dequant_out) return GQ_ERR_INVALID_ARG;
     if (dequant_out && !aligned(norm, 4)) return GQ_ERR_INVALID_ARG;
-    LevelCPtrs Lv;
+    CodePtrs Lv;
     for (int i = 0; i < K; i++) {
         if (d > 0 && !aligned(levels[i], 16)) return GQ_ERR_INVALID_ARG;
         Lv.lv[i] = levels[i];
-        Lv.sp[i] = nullptr;
     }
     if (d > 0 && ((reduced_out && !aligned(reduced_out, 16)) || (dequant_out && !aligned(dequant_out, 16)))) return GQ_ERR_INVALID_ARG;
     if (d == 0) return GQ_OK;
