@@ -27,7 +27,6 @@ constexpr int kNormMaxTileBlocks = 1 << 16;    // cap on the number of tile part
 constexpr int kNormVecPerThread = 8;           // per-worker shape: target loads per thread
 constexpr int kNormMaxBlocksPerWorker = 1024;
 constexpr int kNormFinalBlock = 1024;
-constexpr int kNormFinalRuns = 4;
 
 static inline int norm_blocks_per_worker(int64_t d)
 {
@@ -174,26 +173,16 @@ norm_final_kernel(const uint64_t *__restrict__ partial, int groups, int64_t per_
         uint32_t m = 0;
         double a = 0.0, b = 0.0, c = 0.0, e = 0.0;
         int64_t i = threadIdx.x;
-        // runs of four, kNormFinalRuns of them in flight, then one at a time (the order of the additions is the same)
-        auto take4 = [&](uint64_t p0, uint64_t p1, uint64_t p2, uint64_t p3) {
+        for (; i + 3 * kNormFinalBlock < per_group; i += 4 * kNormFinalBlock) {       // four loads in flight
+            const uint64_t p0 = p[i], p1 = p[i + kNormFinalBlock], p2 = p[i + 2 * kNormFinalBlock], p3 = p[i + 3 * kNormFinalBlock];
             if (kind == 0) m = max(max(m, (uint32_t)p0), max(max((uint32_t)p1, (uint32_t)p2), (uint32_t)p3));
             else { a += __longlong_as_double((long long)p0); b += __longlong_as_double((long long)p1);
                    c += __longlong_as_double((long long)p2); e += __longlong_as_double((long long)p3); }
-        };
-        for (; i + (4 * kNormFinalRuns - 1) * kNormFinalBlock < per_group; i += 4 * kNormFinalRuns * kNormFinalBlock) {
-            uint64_t q[4 * kNormFinalRuns];
-#pragma unroll
-            for (int j = 0; j < 4 * kNormFinalRuns; j++) q[j] = p[i + j * kNormFinalBlock];
-#pragma unroll
-            for (int j = 0; j < kNormFinalRuns; j++) take4(q[4 * j], q[4 * j + 1], q[4 * j + 2], q[4 * j + 3]);
         }
-        for (; i + 3 * kNormFinalBlock < per_group; i += 4 * kNormFinalBlock)
-            take4(p[i], p[i + kNormFinalBlock], p[i + 2 * kNormFinalBlock], p[i + 3 * kNormFinalBlock]);
-        // up to three are left: asked for together (0 is the bit pattern of +0.0, and adds nothing)
-        const uint64_t r0 = i < per_group ? p[i] : 0, r1 = i + kNormFinalBlock < per_group ? p[i + kNormFinalBlock] : 0;
-        const uint64_t r2 = i + 2 * kNormFinalBlock < per_group ? p[i + 2 * kNormFinalBlock] : 0;
-        if (kind == 0) m = max(max(m, (uint32_t)r0), max((uint32_t)r1, (uint32_t)r2));
-        else { a += __longlong_as_double((long long)r0); a += __longlong_as_double((long long)r1); a += __longlong_as_double((long long)r2); }
+        for (; i < per_group; i += kNormFinalBlock) {
+            if (kind == 0) m = max(m, (uint32_t)p[i]);
+            else a += __longlong_as_double((long long)p[i]);
+        }
         const uint64_t mine = kind == 0 ? (uint64_t)wave_max(m) : (uint64_t)__double_as_longlong(wave_sum((a + b) + (c + e)));
         __syncthreads();
         if (lane == 0) sh[wave] = mine;
