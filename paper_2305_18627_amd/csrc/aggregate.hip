@@ -150,63 +150,94 @@ int_aggregate_kernel(CodesOf<PACK> L, int K, int64_t d, int64_t v_begin, void *_
 // Algorithm 1's aggregation step on packed 4-bit codes, for workgroups that lie wholly inside the buffer.  The
 // one-vector-per-lane kernel above moves two bytes per lane and load, which leaves it bound by
 // instruction issue, not by HBM.  Here a lane owns EIGHT coordinates: one 32-bit load of codes (and one
-// byte of sign bits) per worker.  Every byte of codes, together with its two sign bits in the sign-plane
-// format, indexes an LDS table whose entry holds the integer values of both coordinates, each biased to
-// be non-negative, in its two 16-bit halves: one table read and one 32-bit add accumulate two
-// coordinates (the biased sums stay below 2^16 for K <= 64: at most (64 + 128) * 64 resp. (15 + 16) * 64).
+// byte of sign bits) per worker.
+//   TABLE      every byte of codes, together with its two sign bits in the sign-plane format, indexes an LDS table whose
+//       entry holds the integer values of both coordinates, each biased to be non-negative, in its two 16-bit halves: one
+//       table read and one 32-bit add accumulate two coordinates (the biased sums stay below 2^16 for K <= 64: at most
+//       (64 + 128) * 64 resp. (15 + 16) * 64).
+//   otherwise  (two's complement, fewer than kNibTableFrom workers) no table to fill and to wait for: the even and the odd
+//       nibbles of the word are four bytes each.  Linear: a nibble with its top bit flipped is the value + 8, and the
+//       workers' sum fits a byte (at most 15 * 15).  Exponential: a byte permute looks up value + 128 in eight
+//       positive and eight negative values, a third one picks by the nibble's top bit, and the bytes go to 16-bit sums.
 // 32-bit sums are staged in LDS so that the workgroup writes two contiguous runs of 16 bytes per thread;
 // 16-bit sums are 16 bytes per lane already.  Not for the exponential grid in the sign-plane format
 // (values up to 2^14 do not fit the halves): that combination keeps the kernel above.
 // =============================================================================================
 constexpr int kNibBlock = 128;
 constexpr int kNibCoords = 8;
+// Two's complement codes: workers from which the table is no slower.  100e6 coordinates, us without / with it: 16-bit sums
+// K = 4 65 / 68, 8 94.5 / 103 (linear 94 / 100.5), 12 126.5 / 135, 16 163.5 / 163, 24 231.5 / 230, 32 301 / 300; at 350e6 x 32
+// 1080 / 1070 (linear 1087 / 1066); 32-bit sums are equal everywhere (memory).
+constexpr int kNibTableFrom = 16;
 
-template <int SCHEME, bool PLANE>
+// value + 128 of four two's complement nibbles (bits 0..3 of every byte of n) on the exponential grid
+__device__ __forceinline__ uint32_t exp_nibble_values(uint32_t n)
+{
+    const uint32_t which = n & 0x07070707u;
+    const uint32_t pos = __builtin_amdgcn_perm(0xC0A09088u, 0x84828180u, which);       // 64 32 16 8 | 4 2 1 0
+    const uint32_t neg = __builtin_amdgcn_perm(0x7F7E7C78u, 0x70604000u, which);       // -1 -2 -4 -8 | -16 -32 -64 -128
+    return __builtin_amdgcn_perm(neg, pos, ((n >> 1) & 0x04040404u) | 0x03020100u);
+}
+
+template <int SCHEME, bool PLANE, bool TABLE>
 __global__ void __launch_bounds__(kNibBlock)
 int_aggregate_nibble_kernel(CodesOf<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4> L, int K, void *__restrict__ agg_out, int agg_fmt)
 {
     static_assert(!(SCHEME == 1 && PLANE), "exponential sign-plane values do not fit 16-bit halves");
-    constexpr int kEntries = PLANE ? 1024 : 256;
-    constexpr int kBias = PLANE ? 16 : 128;
+    static_assert(TABLE || !PLANE, "magnitudes and their sign bits meet in the table");
+    constexpr int kEntries = !TABLE ? 1 : (PLANE ? 1024 : 256);
+    constexpr int kBias = PLANE ? 16 : (!TABLE && SCHEME == 0 ? 8 : 128);
     __shared__ uint32_t lut[kEntries];
     __shared__ int stage[kNibBlock * kNibCoords];
-    for (int e = threadIdx.x; e < kEntries; e += kNibBlock) {
-        uint32_t entry = 0;
-        for (int h = 0; h < 2; h++) {
-            const int nibble = (e >> (4 * h)) & 15;
-            int val;
-            if (PLANE) {
-                val = nibble;                                             // linear magnitude
-                if ((e >> (8 + h)) & 1) val = -val;
-            } else {
-                const int q = (nibble ^ 8) - 8;                           // two's complement nibble
-                const int mag = (int)((1u << abs(q)) >> 1);               // 2^(k-1), 0 for k = 0
-                val = SCHEME == 0 ? q : (q < 0 ? -mag : mag);
+    if (TABLE) {
+        for (int e = threadIdx.x; e < kEntries; e += kNibBlock) {
+            uint32_t entry = 0;
+            for (int h = 0; h < 2; h++) {
+                const int nibble = (e >> (4 * h)) & 15;
+                int val;
+                if (PLANE) {
+                    val = nibble;                                         // linear magnitude
+                    if ((e >> (8 + h)) & 1) val = -val;
+                } else {
+                    const int q = (nibble ^ 8) - 8;                       // two's complement nibble
+                    const int mag = (int)((1u << abs(q)) >> 1);           // 2^(k-1), 0 for k = 0
+                    val = SCHEME == 0 ? q : (q < 0 ? -mag : mag);
+                }
+                entry |= (uint32_t)(val + kBias) << (16 * h);
             }
-            entry |= (uint32_t)(val + kBias) << (16 * h);
+            lut[e] = entry;
         }
-        lut[e] = entry;
+        __syncthreads();
     }
-    __syncthreads();
-    const int64_t u = (int64_t)blockIdx.x * kNibBlock + threadIdx.x;      // eight coordinates 8u .. 8u+7
+    const int64_t ub = (int64_t)blockIdx.x * kNibBlock;                   // scalar
+    const int64_t u = ub + threadIdx.x;                                   // eight coordinates 8u .. 8u+7
 
-    uint32_t s01 = 0, s23 = 0, s45 = 0, s67 = 0;
+    // biased sums in 16-bit halves: TABLE coordinates (0,1) (2,3) (4,5) (6,7), else (0,4) (1,5) (2,6) (3,7)
+    uint32_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    uint32_t even = 0, odd = 0;                                           // no table, linear: byte sums
     auto add = [&](uint32_t c, uint32_t sb) {
-        if (PLANE) {
-            s01 += lut[(c & 255u) | ((sb & 3u) << 8)];
-            s23 += lut[((c >> 8) & 255u) | ((sb & 12u) << 6)];
-            s45 += lut[((c >> 16) & 255u) | ((sb & 48u) << 4)];
-            s67 += lut[(c >> 24) | ((sb & 192u) << 2)];
+        if constexpr (PLANE) {
+            s0 += lut[(c & 255u) | ((sb & 3u) << 8)];
+            s1 += lut[((c >> 8) & 255u) | ((sb & 12u) << 6)];
+            s2 += lut[((c >> 16) & 255u) | ((sb & 48u) << 4)];
+            s3 += lut[(c >> 24) | ((sb & 192u) << 2)];
+        } else if constexpr (TABLE) {
+            s0 += lut[c & 255u];
+            s1 += lut[(c >> 8) & 255u];
+            s2 += lut[(c >> 16) & 255u];
+            s3 += lut[c >> 24];
+        } else if constexpr (SCHEME == 0) {
+            even += (c & 0x0F0F0F0Fu) ^ 0x08080808u;
+            odd += ((c >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u;
         } else {
-            s01 += lut[c & 255u];
-            s23 += lut[(c >> 8) & 255u];
-            s45 += lut[(c >> 16) & 255u];
-            s67 += lut[c >> 24];
+            const uint32_t e = exp_nibble_values(c), o = exp_nibble_values(c >> 4);
+            s0 += e & 0x00FF00FFu; s2 += (e >> 8) & 0x00FF00FFu;
+            s1 += o & 0x00FF00FFu; s3 += (o >> 8) & 0x00FF00FFu;
         }
     };
-    auto codes_of = [&](int w) { return __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(L.lv[w]) + u); };
+    auto codes_of = [&](int w) { return __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(L.lv[w]) + ub + threadIdx.x); };
     auto signs_of = [&](int w) -> uint32_t {
-        if constexpr (PLANE) return reinterpret_cast<const uint8_t *>(L.sp[w])[u];
+        if constexpr (PLANE) return reinterpret_cast<const uint8_t *>(L.sp[w])[ub + threadIdx.x];
         else return 0u;
     };
     int w = 0;
@@ -231,17 +262,27 @@ int_aggregate_nibble_kernel(CodesOf<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4> L
         w += 2;
     }
     if (w < K) add(codes_of(w), signs_of(w));
+    if constexpr (!TABLE && SCHEME == 0) {
+        s0 = even & 0x00FF00FFu; s2 = (even >> 8) & 0x00FF00FFu;
+        s1 = odd & 0x00FF00FFu; s3 = (odd >> 8) & 0x00FF00FFu;
+    }
     const int off = K * kBias;
-    const int a0 = (int)(s01 & 0xFFFFu) - off, a1 = (int)(s01 >> 16) - off, a2 = (int)(s23 & 0xFFFFu) - off, a3 = (int)(s23 >> 16) - off;
-    const int a4 = (int)(s45 & 0xFFFFu) - off, a5 = (int)(s45 >> 16) - off, a6 = (int)(s67 & 0xFFFFu) - off, a7 = (int)(s67 >> 16) - off;
+    int a[8];
+    if constexpr (TABLE) {
+        a[0] = (int)(s0 & 0xFFFFu) - off; a[1] = (int)(s0 >> 16) - off; a[2] = (int)(s1 & 0xFFFFu) - off; a[3] = (int)(s1 >> 16) - off;
+        a[4] = (int)(s2 & 0xFFFFu) - off; a[5] = (int)(s2 >> 16) - off; a[6] = (int)(s3 & 0xFFFFu) - off; a[7] = (int)(s3 >> 16) - off;
+    } else {
+        a[0] = (int)(s0 & 0xFFFFu) - off; a[4] = (int)(s0 >> 16) - off; a[1] = (int)(s1 & 0xFFFFu) - off; a[5] = (int)(s1 >> 16) - off;
+        a[2] = (int)(s2 & 0xFFFFu) - off; a[6] = (int)(s2 >> 16) - off; a[3] = (int)(s3 & 0xFFFFu) - off; a[7] = (int)(s3 >> 16) - off;
+    }
     if (agg_fmt == GQ_AGG_I16) {
-        const u32x4 o = {((uint32_t)a0 & 0xFFFFu) | ((uint32_t)a1 << 16), ((uint32_t)a2 & 0xFFFFu) | ((uint32_t)a3 << 16),
-                         ((uint32_t)a4 & 0xFFFFu) | ((uint32_t)a5 << 16), ((uint32_t)a6 & 0xFFFFu) | ((uint32_t)a7 << 16)};
+        const u32x4 o = {((uint32_t)a[0] & 0xFFFFu) | ((uint32_t)a[1] << 16), ((uint32_t)a[2] & 0xFFFFu) | ((uint32_t)a[3] << 16),
+                         ((uint32_t)a[4] & 0xFFFFu) | ((uint32_t)a[5] << 16), ((uint32_t)a[6] & 0xFFFFu) | ((uint32_t)a[7] << 16)};
         __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(agg_out) + u);
     } else {
         const int t = (int)threadIdx.x;
-        *reinterpret_cast<i32x4 *>(&stage[8 * t]) = i32x4{a0, a1, a2, a3};
-        *reinterpret_cast<i32x4 *>(&stage[8 * t + 4]) = i32x4{a4, a5, a6, a7};
+        *reinterpret_cast<i32x4 *>(&stage[8 * t]) = i32x4{a[0], a[1], a[2], a[3]};
+        *reinterpret_cast<i32x4 *>(&stage[8 * t + 4]) = i32x4{a[4], a[5], a[6], a[7]};
         __syncthreads();
         i32x4 *out = reinterpret_cast<i32x4 *>(agg_out) + (int64_t)blockIdx.x * (kNibBlock * kNibCoords / 4);
         __builtin_nontemporal_store(*reinterpret_cast<const i32x4 *>(&stage[4 * t]), out + t);
@@ -306,15 +347,19 @@ gq_status gq_int_aggregate(const void *const *levels, const uint32_t *const *sig
     // packed 4-bit codes: the workgroups that lie wholly inside the buffer take the eight-coordinates-per-lane
     // kernel, the ragged rest (fewer than 1024 coordinates) the general one
     int64_t v_begin = 0;
-    const bool nibble_lut = p->pack == GQ_PACK_I4 || (p->pack == GQ_PACK_U4_SIGNPLANE && p->scheme == GQ_LINEAR);
-    if (nibble_lut) {
+    const bool nibble_sum = p->pack == GQ_PACK_I4 || (p->pack == GQ_PACK_U4_SIGNPLANE && p->scheme == GQ_LINEAR);
+    if (nibble_sum) {
         const int64_t wide_blocks = d / (kNibBlock * kNibCoords);
         if (!grid_fits(wide_blocks, kNibBlock)) return GQ_ERR_INVALID_ARG;
         if (wide_blocks > 0) {
             const dim3 wgrid((unsigned)wide_blocks), wblock(kNibBlock);
-            if (p->pack == GQ_PACK_U4_SIGNPLANE) hipLaunchKernelGGL((int_aggregate_nibble_kernel<0, true>), wgrid, wblock, 0, s, L, K, agg_out, p->agg);
-            else if (p->scheme == GQ_LINEAR) hipLaunchKernelGGL((int_aggregate_nibble_kernel<0, false>), wgrid, wblock, 0, s, codes_of_format<GQ_PACK_I4>(L), K, agg_out, p->agg);
-            else hipLaunchKernelGGL((int_aggregate_nibble_kernel<1, false>), wgrid, wblock, 0, s, codes_of_format<GQ_PACK_I4>(L), K, agg_out, p->agg);
+#define GQ_NIB(SC, PLANE, TABLE) hipLaunchKernelGGL((int_aggregate_nibble_kernel<SC, PLANE, TABLE>), wgrid, wblock, 0, s, \
+                                                    codes_of_format<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4>(L), K, agg_out, p->agg)
+            const bool table = K >= kNibTableFrom;
+            if (p->pack == GQ_PACK_U4_SIGNPLANE) GQ_NIB(0, true, true);
+            else if (p->scheme == GQ_LINEAR) { if (table) GQ_NIB(0, false, true); else GQ_NIB(0, false, false); }
+            else { if (table) GQ_NIB(1, false, true); else GQ_NIB(1, false, false); }
+#undef GQ_NIB
             if (launched() != GQ_OK) return GQ_ERR_DEVICE;
             v_begin = wide_blocks * (kNibBlock * kNibCoords / 4);
             if (v_begin >= nvec) return GQ_OK;

@@ -192,3 +192,28 @@ def test_tree_reductions_at_workgroup_edges(kind, s, K, d):
         want = O.avg_tree_reduce(qs, 21, 64)
     want = O.pack(np.asarray(want).astype(np.int8), pack)[0]
     assert np.array_equal(host(red)[:want.size], want) and (host(red)[want.size:] == 0xAB).all()
+
+
+# Packed two's complement nibbles are summed without a table below 16 workers (byte sums on the linear grid, a byte look-up on the
+# exponential one) and through a table from there; every nibble value, also -8, in whole workgroups of 1024 and in the ragged rest.
+@pytest.mark.parametrize("K", [1, 2, 4, 7, 8, 15, 16, 17, 24, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("scheme,lo", [("linear", -8), ("exp", -8)])
+@pytest.mark.parametrize("agg", [0, 1])
+def test_int_aggregate_every_nibble_value(K, scheme, lo, agg):
+    d = 2 * 1024 + 7
+    rng = np.random.default_rng(K)
+    qs = [rng.integers(lo, 8, d).astype(np.int64) for _ in range(K)]
+    for w, q in enumerate(qs):
+        q[:16] = np.arange(-8, 8)                      # all workers alike: the extreme sums
+        q[16:32] = -8
+        q[1024:1040] = 7
+    values = [np.sign(q) * ((1 << np.abs(q)) >> 1) if scheme == "exp" else q for q in qs]
+    want = np.sum(values, axis=0)
+    lvs = []
+    for q in qs:
+        n = np.concatenate([q & 15, [0]]).astype(np.uint8)
+        lvs.append(torch.from_numpy(n[0::2] | (n[1::2] << 4)).to(DEV))
+    p = gq.make_params(0 if scheme == "linear" else 1, 7, gq.GQ_PACK_I4, agg, seed=0)
+    out = torch.full((d + 8,), 77, dtype=torch.int16 if agg else torch.int32, device=DEV)
+    gq.int_aggregate(lvs, None, d, p, out)
+    assert np.array_equal(host(out)[:d].astype(np.int64), want) and (host(out)[d:] == 77).all()
