@@ -104,9 +104,9 @@ typedef struct {
 /* gq_params.flags.  The fused call stores its sums either as each wave finishes or, in large launches, only
  * inside short chip-wide time windows (all waves watch the same 100 MHz counter), which separates the
  * write bursts from the read stream in HBM.  The windows change timing only, never a result.  By default the
- * library uses them where they were measured to pay (K >= 8 and K * d >= 2.5e8, no codes stored).  The two
- * bits override that policy: OFF never waits, ON waits in every launch that stores no codes.  Both
- * bits at once: GQ_ERR_INVALID_ARG.  Every call other than gq_fused_quantize_aggregate (and the bucketed
+ * library uses them where they were measured to pay (K * d >= 2.5e8, no codes stored, and K >= 8, or 10 and 12
+ * where 6 and 8 bytes per coordinate are stored, sum and mean together).  The two bits override that policy: OFF
+ * never waits, ON waits in every launch that stores no codes.  Both bits at once: GQ_ERR_INVALID_ARG.  Every call other than gq_fused_quantize_aggregate (and the bucketed
  * schedule built on it) ignores them. */
 #define GQ_FLAG_WRITE_WINDOWS_OFF 1
 #define GQ_FLAG_WRITE_WINDOWS_ON 2

@@ -104,7 +104,12 @@ template <> struct Acc<false> {
 // batch of four workers, which stops the compiler from hoisting all K loads to the top (it would
 // otherwise, and with every load issued up front the windows were measured to gain nothing).
 constexpr uint32_t kWindowTicksPerWorker = 62;    // ticks of the 100 MHz counter per worker and period
-constexpr int kWindowMinWorkers = 8;
+// The fewest workers for which the windows win, by the bytes written per coordinate: the more is written, the longer a burst
+// and the more reads it takes to pay for the wait.  Windows on against off, 48e6 coordinates: 2 bytes K = 8 +1.1 %, 9 +2.4 %;
+// 4 bytes K = 8 -0.8 % (110e6: +1.0), 9 +0.4, 10 +2.0; 6 bytes K = 9 -0.2, 10 +1.5, 12 +5.1; 8 bytes (32-bit sum and mean)
+// K = 8 -2.6, 9 -3.2, 10 -2.8, 12 +2.3, 16 +3.7.  K = 8 with the mean in buckets of 67e6: 458 with, 438 us without where the
+// gradients are rows of one allocation, 440 either way where each has its own; 22.4 such buckets with their norms 17.26 -> 16.95 ms.
+constexpr int window_min_workers(int bytes) { return bytes <= 4 ? 8 : bytes <= 6 ? 10 : 12; }
 constexpr double kWindowMinLoads = 2.5e8;         // K * d from which the windows win (measured)
 constexpr int kWindowMaxPolls = 1024;             // polls of about 0.2 us each: the longest period (K = 64, short draws) is 79 us
 
@@ -424,7 +429,8 @@ static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L
     // Write windows pay once a launch lasts many periods and a wave's K loads span about one period;
     // below these sizes the wait for the next window costs more than the cleaner read/write mix gains.
     // The caller may override the policy either way (gq_params.flags).
-    const bool by_policy = K >= kWindowMinWorkers && (double)K * (double)d >= kWindowMinLoads;
+    const int out_bytes = (agg_out ? (p->agg == GQ_AGG_I16 ? 2 : 4) : 0) + (deq_out ? 4 : 0);
+    const bool by_policy = K >= window_min_workers(out_bytes) && (double)K * (double)d >= kWindowMinLoads;
     const bool win = !levels && !(p->flags & GQ_FLAG_WRITE_WINDOWS_OFF) && (by_policy || (p->flags & GQ_FLAG_WRITE_WINDOWS_ON));
     const uint32_t win_period = kWindowTicksPerWorker * (uint32_t)K * (uint32_t)kLaneVecs;   // a wave loads kLaneVecs KiB per worker
     const uint32_t win_open = win_period / 10u;
