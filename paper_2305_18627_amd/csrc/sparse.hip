@@ -61,10 +61,11 @@ __device__ __forceinline__ u32x2 load_code_unit(const uint8_t *lv, int64_t t, in
 // counts of a group into its word with them makes a call two to five times slower).
 //   span field   the count of the span, top bit set once it is published
 //   group word   bits 39..0 the sum of the counts of the group's spans, bit 40 set once it is published
-// A block publishes its count as soon as it has counted, before it waits for anybody.  What lies before block b
-// is the sum of all earlier groups plus the counts of the earlier blocks of its own group; the last block of a
-// group, which has just added up its predecessors for itself, publishes the group's word.  No block waits for
-// another block's prefix, so the waits do not chain: a few hundred words are read once or twice per block.
+// A block publishes its count as soon as it has counted, before it waits for anybody.  What lies before block b is the
+// counts of the earlier blocks of its own group and of up to kWindow groups before it, plus the sums of all groups before
+// those; the last block of a group, which has just added up its predecessors for itself, publishes the group's word.
+// No block waits for another block's prefix, so the waits do not chain: a few hundred words are read once or twice per
+// block.
 //
 // Why every wait ends.  One workgroup per span.  Workgroups of a one-dimensional grid are handed to the eight XCDs
 // in turn and each XCD starts its share in increasing order.  Let m be the smallest span not yet finished: every
@@ -77,6 +78,16 @@ __device__ __forceinline__ u32x2 load_code_unit(const uint8_t *lv, int64_t t, in
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kGroupWords = 64;
 constexpr uint64_t kGroupPublished = 1ull << 40;
+// Groups before the own one whose counts are read span by span, in grids of at least kWindowMinGroups groups (us a call on
+// MI355X with 0 / 1 / 4 / 8 / 13 of them; 0 reads group sums only).  The more workgroups lie between a span and the oldest one
+// still running, the more it gains; a short grid only pays for the extra words (12 groups below at 25.6e6, 24 at 50e6 and more).
+//   gq_quantize_compact   110e6: 0.1 % non-zeros 86.3 / 86.9 / 79.7 / 78.7 / 89.8, 21 % 109.9 / 110.0 / 108.4 / 107.0 / 124.5;
+//                         50e6: 42.2 / 42.5 / 40.0 / 40.1 / 47.5, 55.7 / 55.2 / 55.1 / 56.5 / 66.1;
+//                         25.6e6: 25.4 / 25.9 / 25.9 / 26.0 / 27.8, 35.4 / 35.7 / 35.9 / 36.7 / 40.5
+//   gq_compact            110e6: 32.0 / 31.7 / 30.5 / 29.2 / 42.7, 59.8 / 60.5 / 58.8 / 58.0 / 73.9;
+//                         25.6e6: 12.6 / 12.5 / 12.4 / 12.9 / 14.8, 19.6 / 19.6 / 19.9 / 20.7 / 22.5
+constexpr int kWindow = 4;
+constexpr int kWindowMinGroups = 20;
 constexpr int kPrefixMaxPolls = 1 << 21;
 
 // `empty_starts`: the one entry of the table of tile starts of an empty gradient, or nullptr
@@ -111,13 +122,27 @@ __device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_bal
 
 __device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
 
-// Number of non-zero codes before span `span`: the counts of the earlier spans of its own group plus the sums of
-// the earlier groups.  Run by one whole wave; the result is uniform.  Both kinds of word are asked for in the same
-// round trip (a poll queues behind the bulk reads of the whole chip, so trips are what costs).  *in_group receives the
-// own group's part as soon as it is complete and *in_group_ready is set (the caller then publishes the group's sum
-// if it is the group's last span, and calls again for the rest).  Returns true once everything is there, false
-// after an unsuccessful poll; the caller counts those.
-struct Before { uint64_t in_group, groups; bool in_group_ready, groups_ready; int64_t next_group; };
+// Number of non-zero codes before span `span`: the counts of the earlier spans of its own group and of the kWindow groups
+// before it, plus the sums of the groups before those.  Run by one whole wave; the result is uniform.  The counts of
+// the workgroups that run at the same time are so read directly, one trip to memory after they were published; a group's
+// sum, published by its last span a trip later, is only asked for when it is long there.  All words are asked for in the
+// same round trip (a poll queues behind the bulk reads of the whole chip, so trips are what costs), and a group whose
+// counts are complete is not asked for again.
+struct Before {
+    uint64_t total;              // what is known so far
+    uint32_t in_group;           // the own group's part, once bit kWindow of `open` is clear
+    uint32_t open;               // bit j: the counts of group (own - kWindow + j) are still missing
+    int64_t next_group, groups;  // sums of the groups next_group .. groups - 1 are still missing
+};
+
+template <int SPAN> __device__ __forceinline__ Before nothing_known(int64_t span)
+{
+    constexpr int kGroupSpans = kGroupWords * Geometry<SPAN>::kPerWord;
+    const int64_t group = span / kGroupSpans;
+    if (gridDim.x < (unsigned)(kWindowMinGroups * kGroupSpans)) return {0, 0, 1u << kWindow, 0, group};
+    const int first = group < kWindow ? kWindow - (int)group : 0;            // groups of the window that exist: first .. kWindow
+    return {0, 0, ((2u << kWindow) - 1u) & ~((1u << first) - 1u), 0, group < kWindow ? 0 : group - kWindow};
+}
 
 template <int SPAN>
 __device__ __forceinline__ void poll_before(const uint64_t *span_words, const uint64_t *group_words, int64_t span, Before *st)
@@ -126,25 +151,32 @@ __device__ __forceinline__ void poll_before(const uint64_t *span_words, const ui
     const int lane = (int)(threadIdx.x & 63u);
     const int64_t group = span / (kGroupWords * kPerWord);
     const int member = (int)(span - group * (kGroupWords * kPerWord));
-    const int mine = member - lane * kPerWord;               // earlier spans of the group in this lane's word (below 1: none)
-    uint64_t w_in = 0, w_gr = kGroupPublished;
-    if (!st->in_group_ready && mine > 0) w_in = state_load(span_words + group * kGroupWords + lane);
-    if (!st->groups_ready && st->next_group + lane < group) w_gr = state_load(group_words + st->next_group + lane);
-    if (!st->in_group_ready) {
+    uint64_t w[kWindow + 1], w_gr = kGroupPublished;
+    static_for<0, kWindow + 1>([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        const int mine = j < kWindow ? kPerWord : member - lane * kPerWord;  // spans in this lane's word that lie before `span`
+        w[j] = 0;
+        if ((st->open >> j & 1u) != 0u && mine > 0) w[j] = state_load(span_words + (group - kWindow + j) * kGroupWords + lane);
+    });
+    if (st->next_group + lane < st->groups) w_gr = state_load(group_words + st->next_group + lane);
+    static_for<0, kWindow + 1>([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        if ((st->open >> j & 1u) == 0u) return;
+        const int mine = j < kWindow ? kPerWord : member - lane * kPerWord;
         // one field: the flag is the top bit of the upper half, the count the lower half; two: each half has both
-        const uint32_t lo = (uint32_t)w_in, hi = (uint32_t)(w_in >> 32);
+        const uint32_t lo = (uint32_t)w[j], hi = (uint32_t)(w[j] >> 32);
         const bool missing = kPerWord == 1 ? mine > 0 && (hi >> 31) == 0u : (mine > 0 && (lo >> 31) == 0u) || (mine > 1 && (hi >> 31) == 0u);
-        if (ballot(missing) == 0) {
-            const uint32_t sum = kPerWord == 1 ? (mine > 0 ? lo : 0u)
-                                               : (mine > 0 ? lo & 0x7FFFFFFFu : 0u) + (mine > 1 ? hi & 0x7FFFFFFFu : 0u);
-            st->in_group = last_lane(wave_scan(sum));        // at most 2^21
-            st->in_group_ready = true;
-        }
-    }
-    if (!st->groups_ready && ballot(((uint32_t)(w_gr >> 40) & 1u) == 0u) == 0) {
-        st->groups += last_lane(wave_scan((uint32_t)w_gr));  // at most 64 * 2^21
+        if (ballot(missing) != 0) return;
+        const uint32_t sum = kPerWord == 1 ? (mine > 0 ? lo : 0u)
+                                           : (mine > 0 ? lo & 0x7FFFFFFFu : 0u) + (mine > 1 ? hi & 0x7FFFFFFFu : 0u);
+        const uint32_t all = last_lane(wave_scan(sum));                      // at most 2^21
+        if (j == kWindow) st->in_group = all;
+        st->total += all;
+        st->open &= ~(1u << j);
+    });
+    if (st->next_group < st->groups && ballot(((uint32_t)(w_gr >> 40) & 1u) == 0u) == 0) {
+        st->total += last_lane(wave_scan((uint32_t)w_gr));                   // at most 64 * 2^21
         st->next_group += 64;
-        if (st->next_group >= group) st->groups_ready = true;
     }
 }
 
@@ -246,24 +278,24 @@ __device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>
         if (wave != 0) return;
     }
     if (wave == 0) {
-        Before st = {0, 0, false, span / kGroupSpans == 0, 0};
+        Before st = nothing_known<SPAN>(span);
         bool group_sum_out = span % kGroupSpans != kGroupSpans - 1;       // only a group's last span owes one
         int polls = 0;
         bool gave_up = false;
         for (;;) {
             poll_before<SPAN>(span_words, group_words, span, &st);
             // the group's last span publishes the group's sum as soon as it has it, before it waits on
-            if (st.in_group_ready && !group_sum_out) {
+            if ((st.open >> kWindow & 1u) == 0u && !group_sum_out) {
                 if (lane == 0)
-                    __hip_atomic_store(group_words + span / kGroupSpans, kGroupPublished | (st.in_group + span_total), __ATOMIC_RELAXED,
+                    __hip_atomic_store(group_words + span / kGroupSpans, kGroupPublished | (uint64_t)(st.in_group + span_total), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
                 group_sum_out = true;
             }
-            if (st.in_group_ready && st.groups_ready) break;
+            if (st.open == 0u && st.next_group >= st.groups) break;
             if (++polls > kPrefixMaxPolls) { gave_up = true; break; }
             __builtin_amdgcn_s_sleep(4);
         }
-        const uint64_t before = st.in_group + st.groups;
+        const uint64_t before = st.total;
         if (lane == 0) {
             if (gave_up) atomicMax(reinterpret_cast<unsigned long long *>(count_out), ~0ull);
             else if (span == last_span)
@@ -573,6 +605,7 @@ static inline int64_t span_words(int64_t d) { return (d + kWordSpan - 1) / kWord
 // the wait for the spans before them less often.  Where the lines lie (us a call on MI355X, short / long spans):
 //   gq_compact            25.6e6 codes: 0.2 % non-zeros 13.6 / 13.5, 22 % 19.4 / 21.8;  50e6: 19.6 / 17.5, 31.1 / 32.7;  110e6: 39.2 / 33.8, 61 / 62
 //   gq_quantize_compact   25.6e6: 25.0 / 28.8, 35.3 / 40;  110e6: 0.1 % 86.7 / 85.4, 21 % 110 / 115;  300e6: 225 / 217, 300 / 305
+// (both with group sums only for what lies before the own group, kWindow = 0)
 // (one pass of the earlier kernels, spans of 32768 codes on 256 threads: 16.7, 24.8, 25.8, 38.6, 43.1, 64.6 and 34.2, 41.7, 89.7,
 // 115, 220, 298)
 constexpr int64_t kCompactLongFrom = 1ll << 25, kQuantCompactLongFrom = 1ll << 27;

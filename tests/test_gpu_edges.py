@@ -144,6 +144,21 @@ def test_quantize_compact_either_side_of_the_long_spans(d, scale):
     check_quantize_compact_equals_two_calls(x, torch.ones(1, device=DEV), p)
 
 
+# From 20 groups of 64 words on, the counts of the four groups before a span's own are read span by span: a grid one span short
+# of that line, one that ends on it with a span of a single code, one beyond it with a ragged group; the first groups of each
+# have fewer than four before them.
+@pytest.mark.parametrize("scale", [0.002, 0.3])
+@pytest.mark.parametrize("d", [1279 * 32_768, 1279 * 32_768 + 1, 1300 * 32_768 + 77])
+def test_senders_either_side_of_the_window_of_groups(d, scale):
+    x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(6), device=DEV).mul_(scale).clamp_(-1.0, 1.0)
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(gq.GQ_LINEAR, 7, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3)
+    check_quantize_compact_equals_two_calls(x, norm, p)
+    lv = torch.empty(d, dtype=torch.uint8, device=DEV)
+    gq.quantize(x, norm, p, 9, 16, lv)
+    check_lists(host(lv).view(np.int8), lists_of(lv, d, p))
+
+
 # The receiver takes a segment of no more entries than lanes one by one, a longer one four in a row per lane; lists may begin at
 # any element of a buffer (indices 4-byte aligned, values anywhere) and end at the last entry of their capacity.
 @pytest.mark.parametrize("K", [1, 2, 5, 8, 16, 33, 64])
