@@ -169,6 +169,8 @@ constexpr int kNibCoords = 8;
 // K = 4 65 / 68, 8 94.5 / 103 (linear 94 / 100.5), 12 126.5 / 135, 16 163.5 / 163, 24 231.5 / 230, 32 301 / 300; at 350e6 x 32
 // 1080 / 1070 (linear 1087 / 1066); 32-bit sums are equal everywhere (memory).
 constexpr int kNibTableFrom = 16;
+constexpr int nibble_entries(bool plane, bool table) { return !table ? 1 : (plane ? 1024 : 256); }
+constexpr unsigned nibble_lds(bool plane, bool table) { return 4u * (kNibBlock * kNibCoords + nibble_entries(plane, table)); }
 
 // value + 128 of four two's complement nibbles (bits 0..3 of every byte of n) on the exponential grid
 __device__ __forceinline__ uint32_t exp_nibble_values(uint32_t n)
@@ -179,13 +181,26 @@ __device__ __forceinline__ uint32_t exp_nibble_values(uint32_t n)
     return __builtin_amdgcn_perm(neg, pos, ((n >> 1) & 0x04040404u) | 0x03020100u);
 }
 
+// Workgroups per compute unit (of 16), from kNibLimitFrom coordinates on.  us without a limit / with it: 32-bit sums of 150e6
+// coordinates K = 4 145.4 / 141.8, 8 193.0 / 188.3, 16 290.6 / 283.9, 32 503 / 483, 64 965 / 900; with planes 100e6 K = 8 135.7 / 133.3,
+// 32 427 / 418; 16-bit sums K = 16 243.3 / 233.4, 32 447 / 431 (350e6: 1083 / 1025), 64 881 / 860.  The others lose: planes
+// K = 4 102.0 / 103.6, 16-bit sums K = 8 138.9 / 140.2, with planes 108.5 / 114.3.
+constexpr int64_t kNibLimitFrom = 10000000;
+static inline int nibble_workgroups(const gq_params *p, int K, int64_t d)
+{
+    if (d < kNibLimitFrom) return 0;
+    const bool plane = p->pack == GQ_PACK_U4_SIGNPLANE;
+    if (p->agg == GQ_AGG_I16) return !plane && K >= kNibTableFrom ? 12 : 0;
+    return plane ? (K >= 8 ? 12 : 0) : (K >= 8 ? 11 : 12);
+}
+
 template <int SCHEME, bool PLANE, bool TABLE>
 __global__ void __launch_bounds__(kNibBlock)
 int_aggregate_nibble_kernel(CodesOf<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4> L, int K, void *__restrict__ agg_out, int agg_fmt)
 {
     static_assert(!(SCHEME == 1 && PLANE), "exponential sign-plane values do not fit 16-bit halves");
     static_assert(TABLE || !PLANE, "magnitudes and their sign bits meet in the table");
-    constexpr int kEntries = !TABLE ? 1 : (PLANE ? 1024 : 256);
+    constexpr int kEntries = nibble_entries(PLANE, TABLE);
     constexpr int kBias = PLANE ? 16 : (!TABLE && SCHEME == 0 ? 8 : 128);
     __shared__ uint32_t lut[kEntries];
     __shared__ int stage[kNibBlock * kNibCoords];
@@ -353,7 +368,9 @@ gq_status gq_int_aggregate(const void *const *levels, const uint32_t *const *sig
         if (!grid_fits(wide_blocks, kNibBlock)) return GQ_ERR_INVALID_ARG;
         if (wide_blocks > 0) {
             const dim3 wgrid((unsigned)wide_blocks), wblock(kNibBlock);
-#define GQ_NIB(SC, PLANE, TABLE) hipLaunchKernelGGL((int_aggregate_nibble_kernel<SC, PLANE, TABLE>), wgrid, wblock, 0, s, \
+            const int per_cu = nibble_workgroups(p, K, d);
+#define GQ_NIB(SC, PLANE, TABLE) hipLaunchKernelGGL((int_aggregate_nibble_kernel<SC, PLANE, TABLE>), wgrid, wblock, \
+                                                    lds_for_workgroups(per_cu, nibble_lds(PLANE, TABLE)), s, \
                                                     codes_of_format<PLANE ? GQ_PACK_U4_SIGNPLANE : GQ_PACK_I4>(L), K, agg_out, p->agg)
             const bool table = K >= kNibTableFrom;
             if (p->pack == GQ_PACK_U4_SIGNPLANE) GQ_NIB(0, true, true);

@@ -52,4 +52,15 @@ static inline gq_status launched()
 // A launch may hold at most 2^32 - 1 threads in x (HIP's limit on gridDim.x * blockDim.x).
 static inline bool grid_fits(int64_t blocks, int threads) { return blocks >= 0 && blocks * (int64_t)threads <= 0xFFFFFFFFLL; }
 
+// Bytes of dynamic LDS with which no more than `per_cu` workgroups of a kernel that has `used` bytes of its own fit into a
+// compute unit (160 KB, handed out in steps of 1280 bytes); per_cu = 0: no limit.  A kernel that streams from memory and
+// writes a part of what it reads runs below the rate of pure reads, and the more so the more waves are in flight: the
+// writes of one meet the reads of many.  Where arithmetic and latency are hidden by fewer waves, fewer are faster.
+static inline unsigned lds_for_workgroups(int per_cu, unsigned used)
+{
+    if (per_cu <= 0) return 0;
+    const unsigned share = 160u * 1024u / (unsigned)per_cu / 1280u * 1280u;
+    return share > used ? share - used : 0;
+}
+
 }  // namespace gq

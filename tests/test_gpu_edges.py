@@ -232,3 +232,27 @@ def test_int_aggregate_every_nibble_value(K, scheme, lo, agg):
     out = torch.full((d + 8,), 77, dtype=torch.int16 if agg else torch.int32, device=DEV)
     gq.int_aggregate(lvs, None, d, p, out)
     assert np.array_equal(host(out)[:d].astype(np.int64), want) and (host(out)[d:] == 77).all()
+
+
+# Long launches bound the workgroups per compute unit by extra LDS (packed sums from 10e6 coordinates on, the average from 25e6, the
+# fused call from 40e6, the quantiser from 50e6): the same outputs as the same work in short pieces, which are not bounded, in
+# every format and worker count that has a bound of its own.
+PIECE = 6_000_000
+
+
+@pytest.mark.parametrize("K", [4, 8, 16])
+@pytest.mark.parametrize("pack,scheme", [(1, "linear"), (1, "exp"), (3, "linear")])
+@pytest.mark.parametrize("agg", [0, 1])
+def test_packed_sum_long_launch_equals_pieces(K, pack, scheme, agg):
+    d = 10_000_001
+    g = torch.Generator(device=DEV).manual_seed(8)
+    lvs = [torch.randint(0, 256, ((d + 1) // 2 + 16,), generator=g, device=DEV, dtype=torch.int16).to(torch.uint8) for _ in range(K)]
+    sps = [torch.randint(-2**31, 2**31 - 1, ((d + 31) // 32,), generator=g, device=DEV, dtype=torch.int64).to(torch.int32) for _ in range(K)] if pack == 3 else None
+    p = gq.make_params(0 if scheme == "linear" else 1, 7, pack, agg, seed=3)
+    a = torch.full((d,), 77, dtype=torch.int16 if agg else torch.int32, device=DEV)
+    gq.int_aggregate(lvs, sps, d, p, a)
+    for lo in range(0, d, PIECE):
+        n = min(PIECE, d - lo)
+        a1 = torch.empty(n, dtype=a.dtype, device=DEV)
+        gq.int_aggregate([v[lo // 2:] for v in lvs], [v[lo // 32:] for v in sps] if sps else None, n, p, a1)
+        assert torch.equal(a[lo:lo + n], a1)
