@@ -90,6 +90,19 @@ template <> struct Acc<false> {
     __device__ __forceinline__ void pin() { asm volatile("" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : : "memory"); }
 };
 
+// Workgroups per compute unit (of 16) where the worker count is known at compile time, the draws are long and no windows
+// separate reads and writes.  us without a limit / with it: K = 4, linear, 40e6 coordinates 129.7 / 121.6, 67e6 211 / 197 (another
+// card: 212 / 204), 110e6 360 / 329; exponential with 16-bit sum and mean 138.8 / 131.8, 232 / 220 (224 / 226.5); K = 8 with the
+// mean, 67e6: 434 / 415 (452 / 447), exponential with a 16-bit sum 418 / 401.5.  K = 8 without the mean is equal, shorter
+// launches lose (K = 4: 25.6e6 83 / 77 to 90, 6.5e6 21.7 / 23.1), so does K = 16 with its windows (110e6: 1168 / 1394), and
+// short draws are equal.
+constexpr int64_t kFusedLimitFrom = 40000000;
+template <int SCHEME, int KT, bool LEVELS, bool WINDOWS, bool HALF> static inline int fused_workgroups(int64_t coords, bool mean)
+{
+    if (LEVELS || WINDOWS || HALF || coords < kFusedLimitFrom) return 0;
+    return KT == 4 ? (SCHEME == 0 ? 8 : 10) : (KT == 8 && mean ? 8 : 0);
+}
+
 // Write windows.  The kernel reads 4K bytes and writes 4 bytes per coordinate.  With every wave storing
 // whenever it happens to finish, HBM sees writes sprinkled evenly into the read stream and pays a bus
 // turnaround for each; measured on MI355X this mix runs at 5.8-6.1 TB/s while the same reads alone
@@ -438,7 +451,7 @@ static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L
     do {                                                                                                      \
         const int64_t blocks_ = ((COUNT) + kFusedBlock * kLaneVecs - 1) / (kFusedBlock * kLaneVecs);          \
         if (!grid_fits(blocks_, kFusedBlock)) return GQ_ERR_INVALID_ARG;                                                   \
-        hipLaunchKernelGGL((quantize_aggregate_kernel<SCHEME, KT, LV, UH, WIN, HALF>), dim3((unsigned)blocks_), block, 0, st, \
+        hipLaunchKernelGGL((quantize_aggregate_kernel<SCHEME, KT, LV, UH, WIN, HALF>), dim3((unsigned)blocks_), block, lds_for_workgroups(fused_workgroups<SCHEME, KT, LV, WIN, HALF>((COUNT) * 4, deq_out != nullptr), 0), st, \
                            pointers_for<KT>(P), level_ptrs<LV>(L), K, d, (int64_t)(V0), (int64_t)(V0) + (int64_t)(COUNT), norm, p->s, p->seed, worker0,  \
                            call_base, p->pack, agg_out, p->agg, deq_out, div, win_period, win_open);          \
     } while (0)

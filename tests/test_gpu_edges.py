@@ -256,3 +256,21 @@ def test_packed_sum_long_launch_equals_pieces(K, pack, scheme, agg):
         a1 = torch.empty(n, dtype=a.dtype, device=DEV)
         gq.int_aggregate([v[lo // 2:] for v in lvs], [v[lo // 32:] for v in sps] if sps else None, n, p, a1)
         assert torch.equal(a[lo:lo + n], a1)
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("scheme,s,agg,mean", [("linear", 127, 0, True), ("linear", 7, 1, False), ("exp", 7, 1, True), ("exp", 16, 0, False)])
+def test_fused_long_launch_equals_pieces(K, scheme, s, agg, mean):
+    d = 40_000_003
+    g = torch.Generator(device=DEV).manual_seed(8)
+    xs = [torch.randn(d, generator=g, device=DEV).clamp_(-1.0, 1.0) for _ in range(K)]
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(0 if scheme == "linear" else 1, s, gq.GQ_PACK_I8, agg, seed=3)
+    typ = torch.int16 if agg else torch.int32
+    a, m = torch.full((d,), 77, dtype=typ, device=DEV), torch.full((d,), 7.0, device=DEV) if mean else None
+    gq.fused_quantize_aggregate(xs, norm, p, 0, a, m)
+    for lo in range(0, d, PIECE):
+        n = min(PIECE, d - lo)
+        a1, m1 = torch.empty(n, dtype=typ, device=DEV), torch.empty(n, device=DEV) if mean else None
+        gq.fused_quantize_aggregate([x[lo:lo + n] for x in xs], norm, p, lo, a1, m1)
+        assert torch.equal(a[lo:lo + n], a1) and (not mean or torch.equal(m[lo:lo + n], m1))
