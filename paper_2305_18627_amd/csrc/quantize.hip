@@ -423,6 +423,19 @@ quantize_kernel(const float *__restrict__ x, void *__restrict__ lv, uint32_t *__
     else quantize_block<SCHEME, UNIFORM_HI, HALF, false>(x, lv, sp, d, sc, seed, worker, call_base, pack, stage, stage_signs);
 }
 
+// Workgroups per compute unit (of 16) in launches of at least kQuantLimitFrom coordinates: fewer where memory and not
+// arithmetic is the bound, which in the middle of other calls, with the chip's clock up, is the whole linear grid.  Shorter
+// launches lose by their last wave of workgroups (6.5e6: 5 %).  Four calls of 110e6 coordinates between a norm pass and an integer
+// sum, us without a limit / with 12; the four calls in a loop of their own:
+//   linear  int8 757 / 754.5, 351 / 346;  int4 693 / 681, 316 / 310;  8 bits + planes 819 / 814, 356 / 346;  4 bits + planes 706 / 689, 316 / 333
+//   exponential, 8 bits + planes  844 / 825, 358 / 381;  its other formats only lose (with 14: int4 684 / 676, 334 / 346;  4 bits + planes 794 / 790,
+//   347 / 358;  int8 equal, 349 / 359)
+constexpr int64_t kQuantLimitFrom = 50000000;
+static inline int quantize_workgroups(const gq_params *p, int64_t d)
+{
+    return d >= kQuantLimitFrom && (p->scheme == GQ_LINEAR || p->pack == GQ_PACK_U8_SIGNPLANE) ? 12 : 0;
+}
+
 template <bool LEVELS> static inline typename std::conditional<LEVELS, const LevelPtrs &, NoPtrs>::type level_ptrs(const LevelPtrs &L)
 {
     if constexpr (LEVELS) return L;
@@ -530,7 +543,8 @@ gq_status gq_quantize(const float *x, int64_t d, const float *norm, const gq_par
     const bool one_stretch = ((call_base & 0xFFFFFFFFull) + (uint64_t)(blocks * per_block / lane_vecs)) <= ((uint64_t)1 << 32);
     uint32_t *sp = plane ? signplane_out : nullptr;
     hipStream_t st2 = (hipStream_t)hip_stream;
-#define GQ_QUANT(SC, UH, HF) hipLaunchKernelGGL((quantize_kernel<SC, UH, HF>), grid, block, 0, st2, x, levels_out, sp, d, norm, \
+    const unsigned lds = lds_for_workgroups(quantize_workgroups(p, d), kQuantBlock * kQuantVec * 4 + kQuantBlock * kQuantVec / 2);
+#define GQ_QUANT(SC, UH, HF) hipLaunchKernelGGL((quantize_kernel<SC, UH, HF>), grid, block, lds, st2, x, levels_out, sp, d, norm, \
                                                 p->s, p->seed, worker, call_base, p->pack)
 #define GQ_QUANT2(SC, UH) do { if (half) GQ_QUANT(SC, UH, true); else GQ_QUANT(SC, UH, false); } while (0)
     if (p->scheme == GQ_LINEAR) { if (one_stretch) GQ_QUANT2(0, true); else GQ_QUANT2(0, false); }

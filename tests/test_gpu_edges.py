@@ -274,3 +274,26 @@ def test_fused_long_launch_equals_pieces(K, scheme, s, agg, mean):
         a1, m1 = torch.empty(n, dtype=typ, device=DEV), torch.empty(n, device=DEV) if mean else None
         gq.fused_quantize_aggregate([x[lo:lo + n] for x in xs], norm, p, lo, a1, m1)
         assert torch.equal(a[lo:lo + n], a1) and (not mean or torch.equal(m[lo:lo + n], m1))
+
+
+@pytest.mark.parametrize("pack", [0, 1, 2, 3])
+@pytest.mark.parametrize("scheme,s", [("linear", 7), ("exp", 7)])
+@pytest.mark.parametrize("rng_bits", [32, 16])
+def test_quantize_long_launch_equals_pieces(pack, scheme, s, rng_bits):
+    d = 50_000_003
+    x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(8), device=DEV).clamp_(-1.0, 1.0)
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(0 if scheme == "linear" else 1, s, pack, gq.GQ_AGG_I32, seed=3, rng_bits=rng_bits)
+    planes = pack >= 2
+    lv = torch.full((gq.levels_nbytes(d, pack),), 0xAB, dtype=torch.uint8, device=DEV)
+    sp = torch.full(((d + 31) // 32,), -1, dtype=torch.int32, device=DEV) if planes else None
+    gq.quantize(x, norm, p, 2, 0, lv, sp)
+    for lo in range(0, d, PIECE):
+        n = min(PIECE, d - lo)
+        lv1 = torch.empty(gq.levels_nbytes(n, pack), dtype=torch.uint8, device=DEV)
+        sp1 = torch.empty((n + 31) // 32, dtype=torch.int32, device=DEV) if planes else None
+        gq.quantize(x[lo:lo + n], norm, p, 2, lo, lv1, sp1)
+        at = lo if pack in (0, 2) else lo // 2
+        assert torch.equal(lv[at:at + lv1.numel()], lv1)
+        if planes:
+            assert torch.equal(sp[lo // 32:lo // 32 + sp1.numel()], sp1)
