@@ -433,10 +433,10 @@ avg_reduce_kernel(CodePtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_ba
                   float *__restrict__ deq_out)
 {
     constexpr int L = NPAD == 1 ? 0 : NPAD == 2 ? 1 : NPAD == 4 ? 2 : NPAD == 8 ? 3 : NPAD == 16 ? 4 : NPAD == 32 ? 5 : 6;
-    const int64_t block_v = (int64_t)blockIdx.x * kReduceBlock;          // scalar
+    const int64_t block_v = (int64_t)blockIdx.x * blockDim.x;            // scalar
     const int64_t v = block_v + threadIdx.x;
     const int64_t nfull = d >> 2;
-    const bool whole = block_v + kReduceBlock <= nfull;                  // uniform: no lane of the block needs a guard
+    const bool whole = block_v + blockDim.x <= nfull;                    // uniform: no lane of the block needs a guard
     const int nvalid = v < nfull ? 4 : (v == nfull ? (int)(d & 3) : 0);
     if (nvalid == 0) return;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -542,6 +542,18 @@ avg_reduce_kernel(CodePtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_ba
     }
 }
 
+// Threads per workgroup of the averaging kernel, and workgroups per compute unit (0: as many as fit).  Trees of up to eight leaves
+// are as fast or faster in workgroups of 256 (110e6 x 4: 150 us, 155 in 128), larger ones in 128 (12e6 x 16: 40.5, 42.8 in 256; 50e6
+// x 16 in nibbles: 120, 124.5), except for long launches of 16 and more workers' bytes, which are bound by memory and
+// run best with few waves: 110e6 x 16 368 us in 128, 354 in 256 and five a unit; 50e6 x 32 315.5 and 302; 25.6e6 x 16 85.4 and 84.3.
+constexpr int64_t kAverageLimitFrom = 25000000;
+static inline int average_threads(int K, int64_t d, bool nibbles, int *per_cu)
+{
+    const bool few_waves = K >= 16 && !nibbles && d >= kAverageLimitFrom;
+    *per_cu = few_waves ? 5 : 0;
+    return K <= 8 || few_waves ? kReduceBlock : 128;
+}
+
 }  // namespace gq
 
 using namespace gq;
@@ -614,17 +626,20 @@ gq_status gq_avg_reduce(const void *const *levels, int K, int64_t d, const gq_pa
     if (d > 0 && ((reduced_out && !aligned(reduced_out, 16)) || (dequant_out && !aligned(dequant_out, 16)))) return GQ_ERR_INVALID_ARG;
     if (d == 0) return GQ_OK;
     const int64_t nvec = (d + 3) / 4;
-    const int64_t blocks = (nvec + kReduceBlock - 1) / kReduceBlock;
-    if (!grid_fits(blocks, kReduceBlock)) return GQ_ERR_INVALID_ARG;
-    const dim3 grid((unsigned)blocks), block(kReduceBlock);
+    const bool nib = p->pack == GQ_PACK_I4;
+    int per_cu;
+    const int threads = average_threads(K, d, nib, &per_cu);
+    const unsigned lds = lds_for_workgroups(per_cu, 0);
+    const int64_t blocks = (nvec + threads - 1) / threads;
+    if (!grid_fits(blocks, threads)) return GQ_ERR_INVALID_ARG;
+    const dim3 grid((unsigned)blocks), block((unsigned)threads);
     const uint64_t call_base = (uint64_t)index_base / 4u;
-    const bool one_stretch = ((call_base & 0xFFFFFFFFull) + (uint64_t)(blocks * kReduceBlock)) <= ((uint64_t)1 << 32);
+    const bool one_stretch = ((call_base & 0xFFFFFFFFull) + (uint64_t)(blocks * threads)) <= ((uint64_t)1 << 32);
     hipStream_t s = (hipStream_t)hip_stream;
     int npad = 1;
     while (npad < K) npad <<= 1;
     const float div = (float)((int64_t)K * p->s) / (float)npad;          // exact: a power-of-two division
-    const bool nib = p->pack == GQ_PACK_I4;
-#define GQ_AVG3(N, NB, UH) hipLaunchKernelGGL((avg_reduce_kernel<N, NB, UH>), grid, block, 0, s, Lv, K, d, p->seed, \
+#define GQ_AVG3(N, NB, UH) hipLaunchKernelGGL((avg_reduce_kernel<N, NB, UH>), grid, block, lds, s, Lv, K, d, p->seed, \
                                               call_base, norm, div, reduced_out, dequant_out)
 #define GQ_AVG(N)                                                                              \
     do {                                                                                       \

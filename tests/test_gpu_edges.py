@@ -297,3 +297,21 @@ def test_quantize_long_launch_equals_pieces(pack, scheme, s, rng_bits):
         assert torch.equal(lv[at:at + lv1.numel()], lv1)
         if planes:
             assert torch.equal(sp[lo // 32:lo // 32 + sp1.numel()], sp1)
+
+
+@pytest.mark.parametrize("K", [8, 16, 32])
+@pytest.mark.parametrize("pack", [0, 1])
+def test_average_long_launch_equals_pieces(K, pack):
+    d = 25_000_003
+    g = torch.Generator(device=DEV).manual_seed(8)
+    per = 1 if pack == 0 else 2
+    codes = [torch.randint(-7, 8, (d // per + 16,), generator=g, device=DEV, dtype=torch.int16).to(torch.uint8) for _ in range(K)]
+    p = gq.make_params(gq.GQ_LINEAR, 7, pack, gq.GQ_AGG_I32, seed=3)
+    norm = torch.ones(1, device=DEV)
+    red, mean = torch.full((gq.levels_nbytes(d, pack),), 0xAB, dtype=torch.uint8, device=DEV), torch.full((d,), 7.0, device=DEV)
+    gq.avg_reduce(codes, d, p, 0, norm, red, mean)
+    for lo in range(0, d, PIECE):
+        n = min(PIECE, d - lo)
+        red1, mean1 = torch.empty(gq.levels_nbytes(n, pack), dtype=torch.uint8, device=DEV), torch.empty(n, device=DEV)
+        gq.avg_reduce([c[lo // per:] for c in codes], n, p, lo, norm, red1, mean1)
+        assert torch.equal(red[lo // per:lo // per + red1.numel()], red1) and torch.equal(mean[lo:lo + n], mean1)
