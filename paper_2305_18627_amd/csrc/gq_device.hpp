@@ -57,6 +57,7 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+template <bool SCALAR_START = true>
 __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                 uint32_t k0, uint32_t k1)
 {
@@ -66,9 +67,10 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
         // Where c1 and c2 are the same for all lanes, half of the words of the first three rounds are too: written as
         // plain xors, with the uniform operands together, they stay on the scalar unit (the three-input instruction
-        // exists on the vector unit only, and would take the next product there with it).
-        const uint32_t n0 = r < 3 ? (uint32_t)(p1 >> 32) ^ (c1 ^ k0) : xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = r < 3 ? (uint32_t)(p0 >> 32) ^ (c3 ^ k1) : xor3((uint32_t)(p0 >> 32), c3, k1);
+        // exists on the vector unit only, and would take the next product there with it).  Where few waves hide each other's
+        // latency, the scalar products' is the longer one: SCALAR_START off.
+        const uint32_t n0 = SCALAR_START && r < 3 ? (uint32_t)(p1 >> 32) ^ (c1 ^ k0) : xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = SCALAR_START && r < 3 ? (uint32_t)(p0 >> 32) ^ (c3 ^ k1) : xor3((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -255,6 +257,35 @@ __device__ __forceinline__ f32x4 load_coords(const float *x, int64_t v, int nval
     if (nvalid > 1) a.y = t[1];
     if (nvalid > 2) a.z = t[2];
     return a;
+}
+
+// The same without a branch per lane, for launches whose time is latency: vector `li` counted from a workgroup's first (`x`),
+// whose last existing coordinate is x[last].  Every lane loads, past the end the last coordinate again; behind a branch each
+// load would wait for the one before it.  all_asked_for() behind a batch of such loads keeps the scheduler from putting
+// the first one's use before the last one; existing() then zeroes what is past the end.
+__device__ __forceinline__ f32x4 load_clamped(const float *x, uint32_t li, uint32_t last)
+{
+    f32x4 a;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) {
+        const uint32_t c = 4 * li + i;
+        a[i] = x[c < last ? c : last];
+    }
+    return a;
+}
+__device__ __forceinline__ void all_asked_for() { __builtin_amdgcn_sched_barrier(0); }
+__device__ __forceinline__ f32x4 existing(f32x4 a, uint32_t li, uint32_t last)
+{
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) a[i] = 4 * li + i <= last ? a[i] : 0.0f;
+    return a;
+}
+// the last existing coordinate counted from the first of a workgroup that begins at vector vb of d coordinates, as far as 32 bits
+// reach (no workgroup has so many)
+__device__ __forceinline__ uint32_t last_coord(int64_t vb, int64_t d)
+{
+    const int64_t n = d - 1 - (vb << 2);
+    return n < 0x7FFFFFFF ? (uint32_t)n : 0x7FFFFFFFu;
 }
 
 // Short draws: coordinate j of a vector takes the low (j even) or high (j odd) half of word j / 2 of the vector's pair

@@ -103,6 +103,11 @@ template <int SCHEME, int KT, bool LEVELS, bool WINDOWS, bool HALF> static inlin
     return KT == 4 ? (SCHEME == 0 ? 8 : 10) : (KT == 8 && mean ? 8 : 0);
 }
 
+// Launches whose time is latency rather than memory or issue.  At 6.5e6 coordinates the kernels of this file for short launches
+// win and lose by 2 to 4 % (K = 1 9.5 / 9.1 us, K = 4 20.9 / 21.2, K = 32 148 / 153), with the codes stored they lose from 8e6 loads on
+// (K = 8 at 1048576 coordinates 9.3 / 9.3, K = 16 17.6 / 18.4), at 41e6 they lose 4 to 13 %.
+static inline bool short_launch(int K, int64_t d, bool levels) { return d <= 4194304 && (!levels || K * d <= 8388608); }
+
 // Write windows.  The kernel reads 4K bytes and writes 4 bytes per coordinate.  With every wave storing
 // whenever it happens to finish, HBM sees writes sprinkled evenly into the read stream and pays a bus
 // turnaround for each; measured on MI355X this mix runs at 5.8-6.1 TB/s while the same reads alone
@@ -125,6 +130,53 @@ constexpr uint32_t kWindowTicksPerWorker = 62;    // ticks of the 100 MHz counte
 constexpr int window_min_workers(int bytes) { return bytes <= 4 ? 8 : bytes <= 6 ? 10 : 12; }
 constexpr double kWindowMinLoads = 2.5e8;         // K * d from which the windows win (measured)
 constexpr int kWindowMaxPolls = 1024;             // polls of about 0.2 us each: the longest period (K = 64, short draws) is 79 us
+
+// The sums and means of a lane's NV vectors, as far as they exist.
+template <int NV, typename A>
+__device__ __forceinline__ void store_sums(const A (&acc)[NV], const int64_t (&v)[NV], const int (&nvalid)[NV], const Scale &sc, float nrm,
+                                           void *agg_out, int agg_fmt, float *deq_out, float deq_div)
+{
+    const float c = sc.scale != 0.0f ? nrm / deq_div : 0.0f;         // Eq. (1): norm / (n * unit)
+#pragma unroll
+    for (int t = 0; t < NV; t++) {
+        const int nv = nvalid[t];
+        if (nv == 0) break;
+        const i32x4 a = acc[t].get();
+        if (agg_out) {
+            if (agg_fmt == GQ_AGG_I32) {
+                if (nv == 4) {
+                    __builtin_nontemporal_store(a, reinterpret_cast<i32x4 *>(agg_out) + v[t]);
+                } else {
+                    int *o = reinterpret_cast<int *>(agg_out) + (v[t] << 2);
+                    o[0] = a.x;
+                    if (nv > 1) o[1] = a.y;
+                    if (nv > 2) o[2] = a.z;
+                }
+            } else {
+                if (nv == 4) {
+                    const i16x4 o = {(short)a.x, (short)a.y, (short)a.z, (short)a.w};
+                    __builtin_nontemporal_store(o, reinterpret_cast<i16x4 *>(agg_out) + v[t]);
+                } else {
+                    short *o = reinterpret_cast<short *>(agg_out) + (v[t] << 2);
+                    o[0] = (short)a.x;
+                    if (nv > 1) o[1] = (short)a.y;
+                    if (nv > 2) o[2] = (short)a.z;
+                }
+            }
+        }
+        if (deq_out) {
+            if (nv == 4) {
+                const f32x4 o = {(float)a.x * c, (float)a.y * c, (float)a.z * c, (float)a.w * c};
+                __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(deq_out) + v[t]);
+            } else {
+                float *o = deq_out + (v[t] << 2);
+                o[0] = (float)a.x * c;
+                if (nv > 1) o[1] = (float)a.y * c;
+                if (nv > 2) o[2] = (float)a.z * c;
+            }
+        }
+    }
+}
 
 // The launch covers the vectors v0 <= v < vend of the buffers (HALF: v0 = 0).  With UNIFORM_HI the host
 // guarantees that the Philox call index does not cross a multiple of 2^32 inside the launch, so the high
@@ -254,46 +306,123 @@ quantize_aggregate_kernel(GradPtrsFor<KT> P, typename std::conditional<LEVELS, L
             __builtin_amdgcn_s_sleep(8);
         }
     }
-    const float c = sc.scale != 0.0f ? nrm / deq_div : 0.0f;         // Eq. (1): norm / (n * unit)
+    store_sums<NV>(acc, v, nvalid, sc, nrm, agg_out, agg_fmt, deq_out, deq_div);
+}
+
+// Short launches.  Their time is latency: a workgroup has code of its own at the ragged end, so that neither the first worker's
+// arithmetic waits for the loads of all workers nor the guarded loads wait for each other, as they do in the kernel above (two
+// sets of loads beside a branch: one wait for all behind it, and one between any two guarded ones).  us a call, above / here:
+//   100003 coordinates   linear K = 4 3.0 / 2.4, 8 4.45 / 3.25, 16 7.3 / 4.9, 32 11.0 / 8.2;  exponential 3.1 / 2.5, 4.7 / 3.4, 7.6 / 5.1, 12.3 / 8.6;
+//                        short draws, linear 3.8 / 3.1, 5.7 / 4.35, 9.9 / 7.1, 18.3 / 12.7;  int8 codes stored 4.4 / 3.7, 7.1 / 5.6 (K = 4, 8)
+//   1048576 coordinates  linear 4.55 / 4.35, 7.55 / 6.8, 14.8 / 13.3, 29.9 / 26.7;  short draws 4.85 / 4.5, 8.2 / 6.95, 13.5 / 11.5, 25.1 / 23.75
+// WHOLE: every vector of the workgroup exists and nothing is guarded; else the loads are clamped.  The early return and the
+// __restrict__ are needed: without either the scheduler draws the random words of all workers first, in up to 290 registers.
+template <int SCHEME, int KT, bool LEVELS, bool HALF, bool WHOLE>
+__device__ __forceinline__ void
+quantize_aggregate_short_block(const GradPtrsFor<KT> &P, const typename std::conditional<LEVELS, LevelPtrs, NoPtrs>::type &L, int K, int64_t d, int64_t vb,
+                               const float *__restrict__ norm, int s, uint64_t seed, uint32_t worker0, uint64_t call_base, int pack, void *__restrict__ agg_out, int agg_fmt, float *__restrict__ deq_out,
+                               float deq_div)
+{
+    constexpr int NV = HALF ? 2 : 1;             // vectors per lane
+    const int64_t nfull = d >> 2;
+    const int lane = (int)(threadIdx.x & 63u);
+    uint32_t li[NV], local_call;                 // this lane's vectors and its call index relative to the workgroup's first
+    if (HALF) {
+        li[0] = (threadIdx.x >> 6) * 128u + (uint32_t)lane;
+        li[NV - 1] = li[0] + 64u;
+        local_call = (threadIdx.x >> 6) * 64u + (uint32_t)(lane >> 1) + (uint32_t)(lane & 1) * 32u;
+    } else {
+        local_call = li[0] = threadIdx.x;
+    }
+    int64_t v[NV];
+    int nvalid[NV];
 #pragma unroll
     for (int t = 0; t < NV; t++) {
-        const int nv = nvalid[t];
-        if (nv == 0) break;
-        const i32x4 a = acc[t].get();
-        if (agg_out) {
-            if (agg_fmt == GQ_AGG_I32) {
-                if (nv == 4) {
-                    __builtin_nontemporal_store(a, reinterpret_cast<i32x4 *>(agg_out) + v[t]);
-                } else {
-                    int *o = reinterpret_cast<int *>(agg_out) + (v[t] << 2);
-                    o[0] = a.x;
-                    if (nv > 1) o[1] = a.y;
-                    if (nv > 2) o[2] = a.z;
-                }
-            } else {
-                if (nv == 4) {
-                    const i16x4 o = {(short)a.x, (short)a.y, (short)a.z, (short)a.w};
-                    __builtin_nontemporal_store(o, reinterpret_cast<i16x4 *>(agg_out) + v[t]);
-                } else {
-                    short *o = reinterpret_cast<short *>(agg_out) + (v[t] << 2);
-                    o[0] = (short)a.x;
-                    if (nv > 1) o[1] = (short)a.y;
-                    if (nv > 2) o[2] = (short)a.z;
-                }
-            }
-        }
-        if (deq_out) {
-            if (nv == 4) {
-                const f32x4 o = {(float)a.x * c, (float)a.y * c, (float)a.z * c, (float)a.w * c};
-                __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(deq_out) + v[t]);
-            } else {
-                float *o = deq_out + (v[t] << 2);
-                o[0] = (float)a.x * c;
-                if (nv > 1) o[1] = (float)a.y * c;
-                if (nv > 2) o[2] = (float)a.z * c;
-            }
-        }
+        v[t] = vb + li[t];
+        nvalid[t] = WHOLE || v[t] < nfull ? 4 : (v[t] == nfull ? (int)(d & 3) : 0);
     }
+    if (!LEVELS && !HALF && nvalid[0] == 0) return;
+    const uint32_t last = WHOLE ? 0u : last_coord(vb, d);
+    const float nrm = *norm;
+    const Scale sc = make_scale<SCHEME>(nrm, s);
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    const uint64_t first = call_base + (uint64_t)(HALF ? vb >> 1 : vb);           // scalar
+    const uint32_t c_hi = (uint32_t)(first >> 32), c_lo = (uint32_t)first + local_call;     // no carry (host)
+    const int Kc = KT > 0 ? KT : K;
+
+    struct Unit { f32x4 g[NV]; };
+    auto fetch = [&](int w) {
+        Unit x;
+#pragma unroll
+        for (int t = 0; t < NV; t++) {
+            if (WHOLE) x.g[t] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(P.x[w]) + vb + li[t]);
+            else x.g[t] = load_clamped(P.x[w] + (vb << 2), li[t], last);
+        }
+        return x;
+    };
+    Acc<SCHEME == 0 || (KT > 0)> acc[NV];           // exponential with a compile-time K: the host checked the range
+    auto one_worker = [&](int w, const Unit &x) {
+        // the scalar products of the first rounds take longer than the vector unit's where few waves hide them
+        const Words4 r = philox4x32_10<false>(c_lo, c_hi, worker0 + (uint32_t)w, 0u, k0, k1);
+        uint32_t draw[NV][4];
+        if (HALF) {
+            const ShortDraws sd = share_short_draws(r, (lane & 1) != 0);
+#pragma unroll
+            for (int j = 0; j < 4; j++) { draw[0][j] = short_draw(sd.a, j); draw[NV - 1][j] = short_draw(sd.b, j); }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) draw[0][j] = r.w[j];
+        }
+#pragma unroll
+        for (int t = 0; t < NV; t++) {
+            const Quad4<SCHEME> q(LEVELS && !WHOLE ? existing(x.g[t], li[t], last) : x.g[t], sc, draw[t]);
+            acc[t].add(q.v[0], q.v[1], q.v[2], q.v[3]);
+            if constexpr (LEVELS) store_codes<SCHEME>(L.lv[w], L.sp[w], pack, v[t], nvalid[t], d, q);
+        }
+    };
+    // batches whose loads are all issued before the first is consumed
+    constexpr int kBatch = KT == 0 ? (HALF && !WHOLE ? 2 : 4) : (KT < 16 / NV ? KT : 16 / NV);
+    if (KT > 0) {
+#pragma unroll
+        for (int w0 = 0; w0 < KT; w0 += kBatch) {
+            Unit x[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; j++) x[j] = fetch(w0 + j);
+            if (!WHOLE) all_asked_for();
+#pragma unroll
+            for (int j = 0; j < kBatch; j++) one_worker(w0 + j, x[j]);
+            if (HALF) {                              // bounds the loads in flight to one batch
+#pragma unroll
+                for (int t = 0; t < NV; t++) acc[t].pin();
+            }
+        }
+    } else {
+        int w = 0;
+        for (; w + kBatch <= Kc; w += kBatch) {
+            Unit x[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; j++) x[j] = fetch(w + j);
+            if (!WHOLE) all_asked_for();
+#pragma unroll
+            for (int j = 0; j < kBatch; j++) one_worker(w + j, x[j]);
+        }
+        for (; w < Kc; w++) one_worker(w, fetch(w));
+    }
+    if (nvalid[0] == 0) return;
+    store_sums<NV>(acc, v, nvalid, sc, nrm, agg_out, agg_fmt, deq_out, deq_div);
+}
+
+template <int SCHEME, int KT, bool LEVELS, bool HALF>
+__global__ void __launch_bounds__(kFusedBlock)
+quantize_aggregate_short_kernel(GradPtrsFor<KT> P, typename std::conditional<LEVELS, LevelPtrs, NoPtrs>::type L, int K, int64_t d, const float *__restrict__ norm, int s,
+                                uint64_t seed, uint32_t worker0, uint64_t call_base, int pack, void *__restrict__ agg_out, int agg_fmt, float *__restrict__ deq_out, float deq_div)
+{
+    constexpr int kBlockVecs = kFusedBlock * (HALF ? 2 : 1);
+    const int64_t vb = (int64_t)blockIdx.x * kBlockVecs;                     // scalar
+    if (vb + kBlockVecs <= (d >> 2))                                        // uniform over the workgroup
+        quantize_aggregate_short_block<SCHEME, KT, LEVELS, HALF, true>(P, L, K, d, vb, norm, s, seed, worker0, call_base, pack, agg_out, agg_fmt, deq_out, deq_div);
+    else
+        quantize_aggregate_short_block<SCHEME, KT, LEVELS, HALF, false>(P, L, K, d, vb, norm, s, seed, worker0, call_base, pack, agg_out, agg_fmt, deq_out, deq_div);
 }
 
 // =============================================================================================
@@ -482,6 +611,22 @@ static gq_status launch_quantize_aggregate(const GradPtrs &P, const LevelPtrs &L
     // calls of the launch, counting the lanes past the end of whole workgroups
     const uint64_t calls_padded = (uint64_t)((nvec + kFusedBlock * kLaneVecs - 1) / (kFusedBlock * kLaneVecs)) * kFusedBlock;
     const bool one_stretch = ((call_base & 0xFFFFFFFFull) + calls_padded) <= ((uint64_t)1 << 32);
+    if (one_stretch && !win && short_launch(K, d, levels) && !(HALF && levels)) {
+        const int64_t blocks = (nvec + kFusedBlock * kLaneVecs - 1) / (kFusedBlock * kLaneVecs);
+#define GQ_SHORT(KT, LV) hipLaunchKernelGGL((quantize_aggregate_short_kernel<SCHEME, KT, LV, HALF>), dim3((unsigned)blocks), block, 0, st, pointers_for<KT>(P), \
+                                            level_ptrs<LV>(L), K, d, norm, p->s, p->seed, worker0, call_base, p->pack, agg_out, p->agg, deq_out, div)
+        if constexpr (!HALF) {
+            if (levels) { GQ_SHORT(0, true); return launched(); }
+        }
+        if (!float_sum) GQ_SHORT(0, false);
+        else if (K == 4) GQ_SHORT(4, false);
+        else if (K == 8) GQ_SHORT(8, false);
+        else if (K == 16) GQ_SHORT(16, false);
+        else if (K == 32) GQ_SHORT(32, false);
+        else GQ_SHORT(0, false);
+#undef GQ_SHORT
+        return launched();
+    }
     if (levels) {
         // storing codes: one launch; the scalar high word is used when the bucket does not cross 2^32 calls
         if (one_stretch) GQ_LAUNCH(0, true, true, false, 0, nvec);

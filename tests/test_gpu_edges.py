@@ -276,6 +276,67 @@ def test_fused_long_launch_equals_pieces(K, scheme, s, agg, mean):
         assert torch.equal(a[lo:lo + n], a1) and (not mean or torch.equal(m[lo:lo + n], m1))
 
 
+# Up to 2^22 coordinates (with the codes stored up to 2^23 loads) the fused call and the quantiser have kernels of their own: either
+# side of the lines the same outputs as in pieces that lie on the short side, in every worker count with a kernel of its own and
+# where sums pass 2^24 (exponential, s = 22 to 24), and with the windows forced on, which keeps the other kernel.
+@pytest.mark.parametrize("K", [1, 3, 4, 8, 16, 32, 61])
+@pytest.mark.parametrize("scheme,s", [("linear", 127), ("exp", 16), ("exp", 24)])
+@pytest.mark.parametrize("rng_bits", [32, 16])
+@pytest.mark.parametrize("d", [(1 << 22) - 1, 1 << 22, (1 << 22) + 5])
+def test_fused_either_side_of_the_short_launches(K, scheme, s, rng_bits, d):
+    g = torch.Generator(device=DEV).manual_seed(9)
+    pool = torch.randn(d + 64 * 4, generator=g, device=DEV).clamp_(-1.0, 1.0)
+    xs = [pool[4 * w:4 * w + d] for w in range(K)]           # 16-byte aligned, every worker another vector
+    norm = torch.ones(1, device=DEV)
+    sch = 0 if scheme == "linear" else 1
+    p = gq.make_params(sch, s, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3, rng_bits=rng_bits)
+    on = gq.make_params(sch, s, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3, rng_bits=rng_bits, flags=gq.GQ_FLAG_WRITE_WINDOWS_ON)
+    a, b, m = (torch.full((d,), 77, dtype=t, device=DEV) for t in (torch.int32, torch.int32, torch.float32))
+    gq.fused_quantize_aggregate(xs, norm, p, 8, a, m)
+    gq.fused_quantize_aggregate(xs, norm, on, 8, b)
+    assert torch.equal(a, b)
+    for lo in range(0, d, 1_000_008):
+        n = min(1_000_008, d - lo)
+        a1, m1 = torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV)
+        gq.fused_quantize_aggregate([x[lo:lo + n] for x in xs], norm, p, 8 + lo, a1, m1)
+        assert torch.equal(a[lo:lo + n], a1) and torch.equal(m[lo:lo + n], m1)
+
+
+@pytest.mark.parametrize("K,d", [(2, (1 << 22) + 1), (2, 1 << 22), (8, 1 << 20), (8, (1 << 20) + 1), (3, 100_003)])
+@pytest.mark.parametrize("pack", [0, 1, 2, 3])
+@pytest.mark.parametrize("scheme", ["linear", "exp"])
+@pytest.mark.parametrize("rng_bits", [32, 16])
+def test_codes_either_side_of_the_short_launches(K, d, pack, scheme, rng_bits):
+    g = torch.Generator(device=DEV).manual_seed(10)
+    xs = [torch.randn(d, generator=g, device=DEV).clamp_(-1.0, 1.0) for _ in range(K)]
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(0 if scheme == "linear" else 1, 7, pack, gq.GQ_AGG_I32, seed=3, rng_bits=rng_bits)
+    planes = pack >= 2
+
+    def buffers(n):
+        return (torch.full((gq.levels_nbytes(n, pack) + 8,), 0xAB, dtype=torch.uint8, device=DEV),
+                torch.full(((n + 31) // 32 + 1,), -1, dtype=torch.int32, device=DEV) if planes else None)
+
+    codes = [buffers(d) for _ in xs]
+    a = torch.full((d,), 77, dtype=torch.int32, device=DEV)
+    gq.fused_quantize_aggregate(xs, norm, p, 8, a, None, [c[0] for c in codes], [c[1] for c in codes] if planes else None)
+    a2 = torch.empty_like(a)
+    gq.fused_quantize_aggregate(xs, norm, p, 8, a2)
+    assert torch.equal(a, a2)
+    for w, x in enumerate(xs):
+        lv, sp = buffers(d)
+        gq.quantize(x, norm, p, w, 8, lv, sp)
+        assert torch.equal(lv, codes[w][0]) and (not planes or torch.equal(sp, codes[w][1]))
+        for lo in range(0, d, 1_000_000):                    # a multiple of 32: planes and nibbles begin with their words
+            n = min(1_000_000, d - lo)
+            lv1, sp1 = buffers(n)
+            gq.quantize(x[lo:lo + n], norm, p, w, 8 + lo, lv1, sp1)
+            nb, at = gq.levels_nbytes(n, pack), lo if pack in (0, 2) else lo // 2
+            assert torch.equal(lv[at:at + nb], lv1[:nb]) and (lv1[nb:] == 0xAB).all()
+            if planes:
+                assert torch.equal(sp[lo // 32:lo // 32 + (n + 31) // 32], sp1[:-1]) and int(sp1[-1]) == -1
+
+
 @pytest.mark.parametrize("pack", [0, 1, 2, 3])
 @pytest.mark.parametrize("scheme,s", [("linear", 7), ("exp", 7)])
 @pytest.mark.parametrize("rng_bits", [32, 16])
