@@ -93,13 +93,12 @@ struct List {                                                          // a list
 
 typedef c10::SmallVector<void *, GQ_MAX_WORKERS> Pointers;
 
-// Addresses of tensors of at least nbytes each (nbytes < 0: buffers that the call ignores, not looked at); None gives a
-// null address.
+// Addresses of tensors of at least nbytes each; None gives a null address.
 Pointers addresses(const List &l, int64_t nbytes, const char *what)
 {
     Pointers p;
     for (int64_t i = 0; i < l.size(); i++)
-        p.push_back(nbytes < 0 && l[i] != Py_None ? tensor(l[i], what).data_ptr() : need(l[i], nbytes, what));
+        p.push_back(need(l[i], nbytes, what));
     return p;
 }
 Pointers addresses_or_none(PyObject *o, int64_t nbytes, const char *what)
@@ -212,14 +211,15 @@ PyObject *int_aggregate(PyObject *const *a)
     const Params p(a[3]);
     const int64_t d = integer(a[2]);
     const Pointers lv = addresses(List(a[0]), p.levels_nbytes(d), "levels");
-    const Pointers sp = addresses_or_none(a[1], p.planes() ? 4 * ((d + 31) / 32) : -1, "sign plane");
-    if (a[1] != Py_None && sp.size() < lv.size()) {
+    PyObject *planes = p.planes() ? a[1] : Py_None;                    // formats without sign planes ignore them
+    const Pointers sp = addresses_or_none(planes, 4 * ((d + 31) / 32), "sign plane");
+    if (planes != Py_None && sp.size() < lv.size()) {
         PyErr_SetString(PyExc_ValueError, "fewer sign planes than levels");
         throw Refused();
     }
     void *agg = need(a[4], p.agg_bytes() * d, "agg_out"), *st = stream_of(a[5]);
     return call([&] {
-        return lib.gq_int_aggregate_(lv.data(), a[1] == Py_None ? nullptr : reinterpret_cast<const uint32_t *const *>(sp.data()),
+        return lib.gq_int_aggregate_(lv.data(), planes == Py_None ? nullptr : reinterpret_cast<const uint32_t *const *>(sp.data()),
                                      (int)lv.size(), d, p.get(), agg, st);
     });
 }
@@ -241,9 +241,9 @@ PyObject *fused_quantize_aggregate(PyObject *const *a)
     const Params p(a[2]);
     const Gradients g(a[0]);
     void *norm = need(a[1], 4, "norm"), *agg = need(a[4], p.agg_bytes() * g.d, "agg_out"), *mean = need(a[5], 4 * g.d, "dequant_out");
-    const bool levels = a[6] != Py_None, planes = a[7] != Py_None;
+    const bool levels = a[6] != Py_None, planes = levels && p.planes() && a[7] != Py_None;
     const Pointers lv = addresses_or_none(a[6], p.levels_nbytes(g.d), "levels_out");
-    const Pointers sp = addresses_or_none(a[7], levels && p.planes() ? 4 * ((g.d + 31) / 32) : -1, "sign plane");
+    const Pointers sp = addresses_or_none(planes ? a[7] : Py_None, 4 * ((g.d + 31) / 32), "sign plane");
     if ((levels && lv.size() < g.p.size()) || (planes && sp.size() < g.p.size())) {
         PyErr_SetString(PyExc_ValueError, "fewer level buffers or sign planes than gradients");
         throw Refused();

@@ -65,3 +65,43 @@ def test_sequences_streams_and_optional_arguments_reach_the_library_alike():
         gq.global_norm([both[0, :d]] * 65, gq.GQ_NORM_LINF, norm)
     with pytest.raises(ValueError):
         gq.global_norm(both.t()[:K], gq.GQ_NORM_LINF, norm)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pack", [gq.GQ_PACK_I8, gq.GQ_PACK_I4, gq.GQ_PACK_U8_SIGNPLANE, gq.GQ_PACK_U4_SIGNPLANE])
+def test_sign_planes_are_asked_for_where_the_format_has_them(pack):
+    dev = torch.device("cuda:0")
+    K, d = 2, 4099
+    xs = [torch.randn(d, device=dev) for _ in range(K)]
+    norm = torch.zeros(1, device=dev)
+    gq.global_norm(xs, gq.GQ_NORM_LINF, norm)
+    p = gq.make_params(gq.GQ_LINEAR, 7, pack, seed=4)
+    planes = pack >= gq.GQ_PACK_U8_SIGNPLANE
+    lvs = [torch.zeros(gq.levels_nbytes(d, pack), dtype=torch.uint8, device=dev) for _ in xs]
+    sps = [torch.zeros(gq.signplane_nwords(d), dtype=torch.int32, device=dev) for _ in xs]
+    want, got = torch.zeros(d, dtype=torch.int32, device=dev), torch.zeros(d, dtype=torch.int32, device=dev)
+    gq.fused_quantize_aggregate(xs, norm, p, 0, want, None, lvs, sps)
+    gq.int_aggregate(lvs, sps, d, p, got)
+    assert torch.equal(got, want) and int(want.abs().sum()) > 0
+    # one too few, none at all, too short ones: refused where they are used, ignored where not
+    for some in ([], sps[:1], [sps[0], sps[1][:1]]):
+        if planes:
+            with pytest.raises(ValueError):
+                gq.int_aggregate(lvs, some, d, p, got)
+            with pytest.raises(ValueError):
+                gq.fused_quantize_aggregate(xs, norm, p, 0, got, None, lvs, some)
+        else:
+            got.zero_()
+            gq.int_aggregate(lvs, some, d, p, got)
+            assert torch.equal(got, want)
+            got.zero_()
+            gq.fused_quantize_aggregate(xs, norm, p, 0, got, None, lvs, some)
+            assert torch.equal(got, want)
+        got.zero_()
+        gq.fused_quantize_aggregate(xs, norm, p, 0, got, None, None, some)     # no codes stored
+        assert torch.equal(got, want)
+    if planes:
+        with pytest.raises(gq.GQError):
+            gq.int_aggregate(lvs, None, d, p, got)
+    else:
+        gq.int_aggregate(lvs, None, d, p, got)
