@@ -3,8 +3,8 @@
 // What bounds a call on a short gradient is the host, not the GPU: checking and converting the arguments in Python took
 // 4.5 to 6.5 us a call with four workers (10 with sixteen) beside 3.6 to 8 us for the call itself.  Here the same checks
 // take well under a microsecond.  Every function takes its arguments by position, raises ValueError where a tensor does not fit the call, and
-// returns the library's status code.  No reference is kept beyond the call; the interpreter lock is released around the
-// library.
+// returns the library's status code.  The interpreter lock is released around the library; until it returns, the sequences
+// that the addresses came from are kept, and nothing beyond.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <stdint.h>
@@ -81,33 +81,47 @@ struct Params {                                                        // a ctyp
     bool planes() const { return get()->pack >= GQ_PACK_U8_SIGNPLANE; }
 };
 
-struct List {                                                          // a list or tuple, its items borrowed while it lives
-    PyObject *seq;
-    explicit List(PyObject *o) : seq(PySequence_Fast(o, "a list of tensors is wanted")) { if (!seq) throw Refused(); }
-    ~List() { Py_DECREF(seq); }
+// A list, a tuple or another sequence (rows of a tensor among them) as a list or tuple; its items are borrowed while this lives.
+// An iterator has no length and is refused: its tensors may be nobody else's.  None: no list.
+struct List {
+    PyObject *seq = nullptr;
+    explicit List(PyObject *o)
+    {
+        if (o == Py_None) return;
+        if (PyObject_Size(o) < 0 || !(seq = PySequence_Fast(o, "a list of tensors is wanted"))) throw Refused();
+    }
+    ~List() { Py_XDECREF(seq); }
     List(const List &) = delete;
     List &operator=(const List &) = delete;
-    int64_t size() const { return (int64_t)PySequence_Fast_GET_SIZE(seq); }
+    int64_t size() const { return seq ? (int64_t)PySequence_Fast_GET_SIZE(seq) : 0; }
     PyObject *operator[](int64_t i) const { return PySequence_Fast_GET_ITEM(seq, i); }
 };
 
 typedef c10::SmallVector<void *, GQ_MAX_WORKERS> Pointers;
 
-// Addresses of tensors of at least nbytes each; None gives a null address.
-Pointers addresses(const List &l, int64_t nbytes, const char *what)
-{
+// The addresses of a list of tensors of at least nbytes each, the list kept with them; None gives a null address.  A list that the
+// call does not use (`used` false) is not looked at.
+struct Addresses {
+    const List list;
     Pointers p;
-    for (int64_t i = 0; i < l.size(); i++)
-        p.push_back(need(l[i], nbytes, what));
-    return p;
-}
-Pointers addresses_or_none(PyObject *o, int64_t nbytes, const char *what)
+    Addresses(PyObject *o, int64_t nbytes, const char *what, bool used = true) : list(used ? o : Py_None)
+    {
+        for (int64_t i = 0; i < list.size(); i++) p.push_back(need(list[i], nbytes, what));
+    }
+    bool given() const { return list.seq != nullptr; }
+    template <typename T> T *const *as() const { return given() ? reinterpret_cast<T *const *>(p.data()) : nullptr; }
+    int K() const { return (int)p.size(); }
+};
+
+void wanted(PyObject *o)                                               // a list that may not be None
 {
-    if (o == Py_None) return Pointers();
-    return addresses(List(o), nbytes, what);
+    if (o != Py_None) return;
+    PyErr_SetString(PyExc_TypeError, "a list of tensors is wanted, not None");
+    throw Refused();
 }
 
 struct Gradients {
+    const List list;
     Pointers p;
     int64_t d = 0;
     void add(const at::Tensor &t, bool first)
@@ -119,11 +133,11 @@ struct Gradients {
         }
         p.push_back(need(t, 4 * d, "gradient"));
     }
-    explicit Gradients(const at::Tensor &x) { add(x, true); }
-    explicit Gradients(PyObject *o)
+    explicit Gradients(const at::Tensor &x) : list(Py_None) { add(x, true); }
+    explicit Gradients(PyObject *o) : list(o)
     {
-        const List l(o);
-        for (int64_t i = 0; i < l.size(); i++) add(tensor(l[i], "gradient"), i == 0);
+        wanted(o);
+        for (int64_t i = 0; i < list.size(); i++) add(tensor(list[i], "gradient"), i == 0);
     }
     const float *const *x() const { return reinterpret_cast<const float *const *>(p.data()); }
     int K() const { return (int)p.size(); }
@@ -210,17 +224,15 @@ PyObject *int_aggregate(PyObject *const *a)
 {
     const Params p(a[3]);
     const int64_t d = integer(a[2]);
-    const Pointers lv = addresses(List(a[0]), p.levels_nbytes(d), "levels");
-    PyObject *planes = p.planes() ? a[1] : Py_None;                    // formats without sign planes ignore them
-    const Pointers sp = addresses_or_none(planes, 4 * ((d + 31) / 32), "sign plane");
-    if (planes != Py_None && sp.size() < lv.size()) {
+    wanted(a[0]);
+    const Addresses lv(a[0], p.levels_nbytes(d), "levels"), sp(a[1], 4 * ((d + 31) / 32), "sign plane", p.planes());
+    if (sp.given() && sp.K() < lv.K()) {
         PyErr_SetString(PyExc_ValueError, "fewer sign planes than levels");
         throw Refused();
     }
     void *agg = need(a[4], p.agg_bytes() * d, "agg_out"), *st = stream_of(a[5]);
     return call([&] {
-        return lib.gq_int_aggregate_(lv.data(), planes == Py_None ? nullptr : reinterpret_cast<const uint32_t *const *>(sp.data()),
-                                     (int)lv.size(), d, p.get(), agg, st);
+        return lib.gq_int_aggregate_(lv.as<const void>(), sp.as<const uint32_t>(), lv.K(), d, p.get(), agg, st);
     });
 }
 
@@ -241,10 +253,9 @@ PyObject *fused_quantize_aggregate(PyObject *const *a)
     const Params p(a[2]);
     const Gradients g(a[0]);
     void *norm = need(a[1], 4, "norm"), *agg = need(a[4], p.agg_bytes() * g.d, "agg_out"), *mean = need(a[5], 4 * g.d, "dequant_out");
-    const bool levels = a[6] != Py_None, planes = levels && p.planes() && a[7] != Py_None;
-    const Pointers lv = addresses_or_none(a[6], p.levels_nbytes(g.d), "levels_out");
-    const Pointers sp = addresses_or_none(planes ? a[7] : Py_None, 4 * ((g.d + 31) / 32), "sign plane");
-    if ((levels && lv.size() < g.p.size()) || (planes && sp.size() < g.p.size())) {
+    const Addresses lv(a[6], p.levels_nbytes(g.d), "levels_out");
+    const Addresses sp(a[7], 4 * ((g.d + 31) / 32), "sign plane", lv.given() && p.planes());
+    if ((lv.given() && lv.K() < g.K()) || (sp.given() && sp.K() < g.K())) {
         PyErr_SetString(PyExc_ValueError, "fewer level buffers or sign planes than gradients");
         throw Refused();
     }
@@ -252,8 +263,7 @@ PyObject *fused_quantize_aggregate(PyObject *const *a)
     const int64_t base = integer(a[3]);
     return call([&] {
         return lib.gq_fused_quantize_aggregate_(g.x(), g.K(), g.d, (const float *)norm, p.get(), base, agg, (float *)mean,
-                                                levels ? lv.data() : nullptr,
-                                                planes ? reinterpret_cast<uint32_t *const *>(sp.data()) : nullptr, st);
+                                                lv.as<void>(), sp.as<uint32_t>(), st);
     });
 }
 
@@ -281,12 +291,13 @@ template <bool EXP> PyObject *tree_reduce(PyObject *const *a)
 {
     const Params p(a[2]);
     const int64_t d = integer(a[1]), nbytes = EXP ? d : p.levels_nbytes(d);      // Algorithm 2 takes int8 codes
-    const Pointers lv = addresses(List(a[0]), nbytes, "levels");
+    wanted(a[0]);
+    const Addresses lv(a[0], nbytes, "levels");
     void *red = need(a[5], nbytes, "reduced_out"), *mean = need(a[6], 4 * d, "dequant_out"), *norm = need(a[4], 4, "norm");
     void *st = stream_of(a[7]);
     const int64_t base = integer(a[3]);
     return call([&] {
-        return (EXP ? lib.gq_exp_reduce_ : lib.gq_avg_reduce_)(lv.data(), (int)lv.size(), d, p.get(), base, (const float *)norm, red,
+        return (EXP ? lib.gq_exp_reduce_ : lib.gq_avg_reduce_)(lv.as<const void>(), lv.K(), d, p.get(), base, (const float *)norm, red,
                                                                (float *)mean, st);
     });
 }
@@ -345,6 +356,7 @@ PyObject *sparse_aggregate(PyObject *const *a)
 {
     const Params p(a[4]);
     const int64_t d = integer(a[3]);
+    for (int i = 0; i < 3; i++) wanted(a[i]);
     const List il(a[0]), vl(a[1]), cl(a[2]);
     if (vl.size() < il.size() || cl.size() < il.size()) {
         PyErr_SetString(PyExc_ValueError, "fewer values or counts than index lists");
@@ -359,8 +371,8 @@ PyObject *sparse_aggregate(PyObject *const *a)
         val.push_back(need(vl[i], t.numel(), "values"));
         cnt.push_back(need(cl[i], 8, "count"));
     }
-    const Pointers starts = addresses_or_none(a[6], 4 * lib.gq_tile_starts_len_(d), "tile_starts");
-    if (a[6] != Py_None && starts.size() < idx.size()) {
+    const Addresses starts(a[6], 4 * lib.gq_tile_starts_len_(d), "tile_starts");
+    if (starts.given() && starts.K() < (int)idx.size()) {
         PyErr_SetString(PyExc_ValueError, "fewer tables of tile starts than index lists");
         throw Refused();
     }
@@ -368,8 +380,7 @@ PyObject *sparse_aggregate(PyObject *const *a)
     return call([&] {
         return lib.gq_sparse_aggregate_(reinterpret_cast<const uint32_t *const *>(idx.data()), reinterpret_cast<const int8_t *const *>(val.data()),
                                         reinterpret_cast<const uint64_t *const *>(cnt.data()), cap.data(),
-                                        a[6] == Py_None ? nullptr : reinterpret_cast<const uint32_t *const *>(starts.data()),
-                                        (int)idx.size(), d, p.get(), agg, st);
+                                        starts.as<const uint32_t>(), (int)idx.size(), d, p.get(), agg, st);
     });
 }
 

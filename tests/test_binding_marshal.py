@@ -24,34 +24,50 @@ def test_refuses_what_is_not_a_fitting_cuda_tensor():
             gq.global_norm_static([bad], 0, n)
     with pytest.raises(TypeError):
         gq.dequantize(x, 8, n, b"not params", 1, x)
+    # an iterator has no length, and its tensors may be nobody else's
+    for call in (lambda it: gq.global_norm_static(it, 0, n), lambda it: gq.global_norm(it, 0, n, workspace=x), lambda it: gq.int_aggregate(it, None, 8, p, x),
+                 lambda it: gq.int_aggregate([], it, 8, gq.make_params(gq.GQ_LINEAR, 7, gq.GQ_PACK_U4_SIGNPLANE), x),
+                 lambda it: gq.fused_quantize_aggregate(it, n, p, 0, x), lambda it: gq.exp_reduce(it, 8, p, 0, n, x),
+                 lambda it: gq.avg_reduce(it, 8, p, 0, n, x), lambda it: gq.sparse_aggregate(it, [], [], 8, p, x)):
+        with pytest.raises(TypeError):
+            call(t for t in ())
+        with pytest.raises((TypeError, ValueError)):
+            call(t for t in (x,))
 
 
 @pytest.mark.gpu
 def test_sequences_streams_and_optional_arguments_reach_the_library_alike():
     dev = torch.device("cuda:0")
-    K, d = 3, 5003
-    both = torch.randn(K, 5008, device=dev)
-    rows = [both[i, :d] for i in range(K)]
+    K, d = 3, 5008                                     # rows of one tensor are 16-byte aligned
+    both = torch.randn(K, d, device=dev)
+    rows = [both[i] for i in range(K)]
+
+    class Sequence:                                    # has a length and items, and nobody else holds these tensors
+        def __len__(self):
+            return K
+
+        def __getitem__(self, i):
+            if i >= K:
+                raise IndexError(i)
+            return both[i].clone()
+
     ref = None
     side = torch.cuda.Stream()
     p = gq.make_params(gq.GQ_LINEAR, 127, seed=4)
-    for xs in (rows, tuple(rows), both[:, :5004].contiguous()[:, :d].contiguous()):
-        if isinstance(xs, torch.Tensor):               # rows of one tensor, kept 16-byte aligned
-            xs = both[:, :5008]
+    for xs in (rows, tuple(rows), both, Sequence()):
         for stream in (None, torch.cuda.current_stream(), torch.cuda.current_stream().cuda_stream, side, side.cuda_stream):
             side.wait_stream(torch.cuda.current_stream())
-            n = xs[0].numel()
             norm, flags = torch.zeros(1, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
-            agg, mean = torch.zeros(n, dtype=torch.int32, device=dev), torch.zeros(n, device=dev)
+            agg, mean = torch.zeros(d, dtype=torch.int32, device=dev), torch.zeros(d, device=dev)
             torch.cuda.synchronize()
             ws = gq.global_norm(xs, gq.GQ_NORM_LINF, norm, flags, stream=stream)
-            assert ws.numel() >= gq.norm_workspace_bytes(K, n)
+            assert ws.numel() >= gq.norm_workspace_bytes(K, d)
             gq.fused_quantize_aggregate(xs, norm, p, 0, agg, mean, stream=stream)
             torch.cuda.synchronize()
-            got = (norm, flags, agg[:d], mean[:d])
-            if n == d:
-                ref = ref or got
-                assert all(torch.equal(a, b) for a, b in zip(got, ref))
+            got = (norm, flags, agg, mean)
+            ref = ref or got
+            assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    assert float(ref[0]) == float(both.abs().max())
     with torch.cuda.stream(side):                      # None is the stream that is current where the call is made
         norm2 = torch.zeros(1, device=dev)
         gq.global_norm_static(rows, gq.GQ_NORM_LINF, norm2)
@@ -62,7 +78,7 @@ def test_sequences_streams_and_optional_arguments_reach_the_library_alike():
     with pytest.raises(ValueError):
         gq.fused_quantize_aggregate(rows, norm, p, 0, agg, None, [torch.zeros(d, dtype=torch.uint8, device=dev)] * 2)
     with pytest.raises(gq.GQError):
-        gq.global_norm([both[0, :d]] * 65, gq.GQ_NORM_LINF, norm)
+        gq.global_norm([both[0]] * 65, gq.GQ_NORM_LINF, norm)
     with pytest.raises(ValueError):
         gq.global_norm(both.t()[:K], gq.GQ_NORM_LINF, norm)
 
