@@ -84,10 +84,22 @@ _lib = None
 _lib = _load()
 
 
-from . import _marshal as _m  # noqa: E402
+try:
+    from . import _marshal as _m  # noqa: E402
+except ImportError as e:
+    raise ImportError("%s does not load with torch %s: build it again" % (MARSHAL_PATH, torch.__version__)) from e
+if not _m.built_for.startswith("torch %s, " % torch.__version__):
+    raise ImportError("%s was built for %s, this is torch %s: build it again" % (MARSHAL_PATH, _m.built_for, torch.__version__))
 
-_m.bind({name: C.cast(getattr(_lib, name), C.c_void_p).value for name in EXPORTS}, torch._C._cuda_getDevice,
-        torch._C._cuda_getCurrentRawStream)
+
+def _current_raw_stream(device):
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# torch's own functions behind these two skip the Python objects; a torch without a GPU part has neither
+_m.bind({name: C.cast(getattr(_lib, name), C.c_void_p).value for name in EXPORTS},
+        getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),
+        getattr(torch._C, "_cuda_getCurrentRawStream", _current_raw_stream))
 
 
 def lib():

@@ -26,9 +26,20 @@ FLAGS = [
 ]
 
 
+def built_for():
+    """The torch and the interpreter whose C++ and C interfaces _marshal.so is compiled against."""
+    import platform
+
+    import torch
+    return "torch %s, python %s" % (torch.__version__, platform.python_version())
+
+
 def is_stale():
     if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
+    with open(MARSHAL, "rb") as f:
+        if built_for().encode() not in f.read():
+            return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
     return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS + [MARSHAL_SOURCE])
 
@@ -41,7 +52,7 @@ def _build_marshal(verbose):
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = MARSHAL + ".tmp.%d" % os.getpid()
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DGQ_BUILT_FOR="%s"' % built_for(),
           "-I", os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", sysconfig.get_paths()["include"],
           "-o", tmp, MARSHAL_SOURCE, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10"], verbose)
     os.replace(tmp, MARSHAL)

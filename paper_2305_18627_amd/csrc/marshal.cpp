@@ -11,6 +11,10 @@
 
 #include "gqsgd.h"
 
+#ifndef GQ_BUILT_FOR
+#error "GQ_BUILT_FOR names the torch and the interpreter that this is compiled for"
+#endif
+
 namespace {
 
 // the library's entry points, by their addresses in the copy that the binding loaded
@@ -428,4 +432,9 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit__marshal(void)
+{
+    PyObject *m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "built_for", GQ_BUILT_FOR) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -35,6 +35,18 @@ def test_refuses_what_is_not_a_fitting_cuda_tensor():
             call(t for t in (x,))
 
 
+def test_the_marshalling_says_what_it_was_built_for():
+    from paper_2305_18627_amd import binding, build
+    assert binding._m.built_for == build.built_for() and torch.__version__ in binding._m.built_for
+    assert not build.is_stale()
+    real = build.built_for
+    try:                                               # another torch: the library has to be built again
+        build.built_for = lambda: "torch 0.0, python 0.0"
+        assert build.is_stale()
+    finally:
+        build.built_for = real
+
+
 @pytest.mark.gpu
 def test_sequences_streams_and_optional_arguments_reach_the_library_alike():
     dev = torch.device("cuda:0")
