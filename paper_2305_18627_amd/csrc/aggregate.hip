@@ -184,11 +184,12 @@ __device__ __forceinline__ uint32_t exp_nibble_values(uint32_t n)
 // Workgroups per compute unit (of 16), from kNibLimitFrom coordinates on.  us without a limit / with it: 32-bit sums of 150e6
 // coordinates K = 4 145.4 / 141.8, 8 193.0 / 188.3, 16 290.6 / 283.9, 32 503 / 483, 64 965 / 900; with planes 100e6 K = 8 135.7 / 133.3,
 // 32 427 / 418; 16-bit sums K = 16 243.3 / 233.4, 32 447 / 431 (350e6: 1083 / 1025), 64 881 / 860.  The others lose: planes
-// K = 4 102.0 / 103.6, 16-bit sums K = 8 138.9 / 140.2, with planes 108.5 / 114.3.
+// K = 4 102.0 / 103.6, 16-bit sums K = 8 138.9 / 140.2, with planes 108.5 / 114.3, 32-bit sums of 100e6 K = 1 78 / 88, 2 81 / 86
+// (they write more than they read).
 constexpr int64_t kNibLimitFrom = 10000000;
 static inline int nibble_workgroups(const gq_params *p, int K, int64_t d)
 {
-    if (d < kNibLimitFrom) return 0;
+    if (d < kNibLimitFrom || K < 4) return 0;
     const bool plane = p->pack == GQ_PACK_U4_SIGNPLANE;
     if (p->agg == GQ_AGG_I16) return !plane && K >= kNibTableFrom ? 12 : 0;
     return plane ? (K >= 8 ? 12 : 0) : (K >= 8 ? 11 : 12);

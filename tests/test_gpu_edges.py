@@ -240,7 +240,7 @@ def test_int_aggregate_every_nibble_value(K, scheme, lo, agg):
 PIECE = 6_000_000
 
 
-@pytest.mark.parametrize("K", [4, 8, 16])
+@pytest.mark.parametrize("K", [1, 4, 8, 16])
 @pytest.mark.parametrize("pack,scheme", [(1, "linear"), (1, "exp"), (3, "linear")])
 @pytest.mark.parametrize("agg", [0, 1])
 def test_packed_sum_long_launch_equals_pieces(K, pack, scheme, agg):
