@@ -500,7 +500,6 @@ constexpr int kSparseQuads = 2;
 constexpr int64_t kSparseMost = 1 << 30;                 // entries of a segment (a sorted list has at most kSparseSpan)
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));     // entries begin anywhere in their lists
 typedef uint32_t u32_a1 __attribute__((aligned(1)));
-struct Quad { u32x4_a4 idx; uint32_t v0, v1, v2, n; };  // n entries; their codes are v0 | v1 << 8 | v2 << 16
 constexpr int kSparseSpan = 2 * kCompactTile;            // two tiles of the sender's table of tile starts
 
 template <int SCHEME>
@@ -553,36 +552,37 @@ sparse_span_kernel(SparseLists S, int K, int lanes_per_worker, int64_t d, int *_
             const uint32_t j = index - (uint32_t)lo;
             if (j < (uint32_t)kSparseSpan) atomicAdd(&span[j], v);     // always true for a sorted list
         };
-        // four entries in a row per lane, kSparseQuads such quads in flight; a segment of no more entries than lanes: one each
-        if (n <= (uint32_t)lanes_per_worker) {
-            if ((uint32_t)slot < n) add_entry(idx[slot], val[slot]);
+        // four entries in a row per lane, kSparseQuads such quads in flight; a segment of no more than two entries per lane:
+        // a lane's two, both asked for at once (past the end the last one again)
+        if (n <= 2u * (uint32_t)lanes_per_worker) {
+            if ((uint32_t)slot < n) {
+                const uint32_t second = (uint32_t)slot + (uint32_t)lanes_per_worker, at = second < n ? second : n - 1u;
+                const uint32_t i0 = idx[slot], i1 = idx[at];
+                const int q0 = val[slot], q1 = val[at];
+                add_entry(i0, q0);
+                if (second < n) add_entry(i1, q1);
+            }
             n = 0;
         }
+        // A quad that would reach past the segment is the last four entries instead (n > lanes_per_worker >= 8), of which
+        // those before `at` belong to other lanes: no second set of loads behind a branch, which would wait for the first.
         const uint32_t step = 4u * (uint32_t)lanes_per_worker;
         for (uint32_t e = 4u * (uint32_t)slot; e < n; e += kSparseQuads * step) {
-            Quad t[kSparseQuads];
+            u32x4_a4 index[kSparseQuads];
+            uint32_t codes[kSparseQuads], others[kSparseQuads];
 #pragma unroll
             for (int u = 0; u < kSparseQuads; u++) {
-                const uint32_t at = e + u * step;
-                t[u].n = at < n ? (n - at < 4u ? n - at : 4u) : 0u;
-                t[u].v0 = t[u].v1 = t[u].v2 = 0;
-                if (t[u].n == 4u) {
-                    t[u].idx = *reinterpret_cast<const u32x4_a4 *>(idx + at);
-                    t[u].v0 = *reinterpret_cast<const u32_a1 *>(val + at);
-                } else if (t[u].n != 0u) {
-                    // the list may end here: single loads, the missing ones those of the segment's first entry again
-                    const uint32_t a1 = t[u].n > 1u ? at + 1u : 0u, a2 = t[u].n > 2u ? at + 2u : 0u;
-                    t[u].idx = u32x4_a4{idx[at], idx[a1], idx[a2], 0u};
-                    t[u].v0 = (uint8_t)val[at]; t[u].v1 = (uint8_t)val[a1]; t[u].v2 = (uint8_t)val[a2];
-                }
+                const uint32_t at = e + u * step, from = at < n - 4u ? at : n - 4u;
+                others[u] = at - from;
+                index[u] = *reinterpret_cast<const u32x4_a4 *>(idx + from);
+                codes[u] = *reinterpret_cast<const u32_a1 *>(val + from);
             }
 #pragma unroll
             for (int u = 0; u < kSparseQuads; u++) {
-                const uint32_t v = t[u].v0 | (t[u].v1 << 8) | (t[u].v2 << 16);
-                if (t[u].n > 0u) add_entry(t[u].idx.x, (int8_t)v);
-                if (t[u].n > 1u) add_entry(t[u].idx.y, (int8_t)(v >> 8));
-                if (t[u].n > 2u) add_entry(t[u].idx.z, (int8_t)(v >> 16));
-                if (t[u].n > 3u) add_entry(t[u].idx.w, (int8_t)(v >> 24));
+                if (others[u] == 0u) add_entry(index[u].x, (int8_t)codes[u]);
+                if (others[u] <= 1u) add_entry(index[u].y, (int8_t)(codes[u] >> 8));
+                if (others[u] <= 2u) add_entry(index[u].z, (int8_t)(codes[u] >> 16));
+                if (others[u] <= 3u) add_entry(index[u].w, (int8_t)(codes[u] >> 24));
             }
         }
     }

@@ -159,10 +159,10 @@ def test_senders_either_side_of_the_window_of_groups(d, scale):
     check_lists(host(lv).view(np.int8), lists_of(lv, d, p))
 
 
-# The receiver takes a segment of no more entries than lanes one by one, a longer one four in a row per lane; lists may begin at
+# The receiver takes a segment of no more than two entries per lane one by one, a longer one four in a row per lane; lists may begin at
 # any element of a buffer (indices 4-byte aligned, values anywhere) and end at the last entry of their capacity.
 @pytest.mark.parametrize("K", [1, 2, 5, 8, 16, 33, 64])
-@pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 31, 33, 63, 64, 65, 511, 513, 514, 515, 2050, 8192])
+@pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 15, 16, 17, 18, 19, 31, 33, 63, 64, 65, 127, 129, 511, 513, 514, 515, 1023, 1024, 1025, 1026, 2050, 8192])
 @pytest.mark.parametrize("tables", [True, False])
 def test_sparse_aggregate_segment_lengths_and_offsets(K, n, tables):
     d = 2 * 8192 + 5
