@@ -276,8 +276,9 @@ gq_status gq_avg_reduce(const void *const *levels /* host */, int K, int64_t d, 
  *   workspace        device scratch of at least gq_compact_workspace_bytes(d) bytes, 8-byte aligned, overwritten (the
  *                    words of a scan over spans of 32768 codes); not to be shared by calls that may overlap
  * The codes are read once and only the list is written.  The result is unique (sorted by index) and does not
- * depend on scheduling.  count_out = 2^64 - 1 reports that the scan over the blocks gave up waiting (it cannot
- * in a working launch: every block waits only for blocks that started before it); the lists are then incomplete. */
+ * depend on scheduling, nor on other calls that share the GPU.  count_out = 2^64 - 1 reports that the scan over the
+ * blocks gave up waiting (it cannot in a working launch: a block that has waited long for another's count takes that
+ * count itself); the lists are then incomplete. */
 size_t gq_compact_workspace_bytes(int64_t d);
 int64_t gq_tile_starts_len(int64_t d);          /* ceil(d / 4096) + 1; 0 if d is out of range */
 gq_status gq_compact(const void *levels, int64_t d, const gq_params *p /* host */, uint32_t *indices_out,
@@ -289,7 +290,10 @@ gq_status gq_compact(const void *levels, int64_t d, const gq_params *p /* host *
  * starts, bit for bit, from the same rounding rule and random stream -- without the dense codes ever reaching
  * memory: 4 d bytes read, 5 bytes per non-zero written.
  *   x, norm, worker, index_base   as for gq_quantize (p->pack must be GQ_PACK_I8; both settings of p->rng_bits)
- *   the other arguments           as for gq_compact; indices count from x[0]; d <= 2^32 - 1 */
+ *   the other arguments           as for gq_compact; indices count from x[0]; d <= 2^32 - 1
+ * Two calls of this function that may overlap on one GPU (different streams) can each hold the compute units that the
+ * other's scan waits for, if the GPU hands them out that way: order them, or take count_out = 2^64 - 1 (after a few
+ * seconds) as the request to call again.  A call on its own, or beside any other function, always ends with its list. */
 gq_status gq_quantize_compact(const float *x, int64_t d, const float *norm, const gq_params *p /* host */,
                               uint32_t worker, int64_t index_base, uint32_t *indices_out, int8_t *values_out,
                               int64_t capacity, uint64_t *count_out, uint32_t *tile_starts_out,

@@ -11,6 +11,9 @@ SOURCES = [os.path.join(CSRC, f) for f in ("common.hip", "norm.hip", "quantize.h
                                            "sparse.hip", "pipeline.hip")]
 MARSHAL = os.path.join(HERE, "_marshal.so")
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
+# for a test: gq_compact with a third of its spans mute (GQ_MUTE_SPANS in sparse.hip); nothing else loads it
+MUTE_LIB = os.path.join(HERE, "libgqsgd_mute.so")
+MUTE_SOURCES = [os.path.join(CSRC, f) for f in ("common.hip", "sparse.hip")]
 HEADERS = [os.path.join(CSRC, "gq_device.hpp"), os.path.join(CSRC, "gq_host.hpp"),
            os.path.join(ROOT, "include", "gqsgd.h")]
 
@@ -35,12 +38,12 @@ def built_for():
 
 
 def is_stale():
-    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL) or not os.path.exists(MUTE_LIB):
         return True
     with open(MARSHAL, "rb") as f:
         if built_for().encode() not in f.read():
             return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    t = min(os.path.getmtime(f) for f in (LIB, MARSHAL, MUTE_LIB))
     return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS + [MARSHAL_SOURCE])
 
 
@@ -56,6 +59,12 @@ def _build_marshal(verbose):
           "-I", os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", sysconfig.get_paths()["include"],
           "-o", tmp, MARSHAL_SOURCE, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10"], verbose)
     os.replace(tmp, MARSHAL)
+
+
+def _build_mute(verbose):
+    tmp = MUTE_LIB + ".tmp.%d" % os.getpid()
+    _run([HIPCC] + FLAGS + ["-DGQ_MUTE_SPANS=3", "-shared", "-o", tmp] + MUTE_SOURCES, verbose)
+    os.replace(tmp, MUTE_LIB)
 
 
 def _run(cmd, verbose):
@@ -80,10 +89,11 @@ def build(force=True, verbose=False):
     os.makedirs(objdir, exist_ok=True)
     objs = [os.path.join(objdir, os.path.basename(src)[:-4] + ".%d.o" % os.getpid()) for src in SOURCES]
     try:
-        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
-            marshal = ex.submit(_build_marshal, verbose)
+        with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 2)) as ex:
+            marshal, muted = ex.submit(_build_marshal, verbose), ex.submit(_build_mute, verbose)
             list(ex.map(lambda so: _run([HIPCC] + FLAGS + ["-c", "-o", so[1], so[0]], verbose), zip(SOURCES, objs)))
             marshal.result()
+            muted.result()
         tmp = LIB + ".tmp.%d" % os.getpid()
         _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, verbose)
         os.replace(tmp, LIB)

@@ -23,6 +23,10 @@ constexpr int kRow = 512;                               // codes whose entries a
 constexpr int kCompactWaves = 8;                        // waves per workgroup
 constexpr int kStage = kCompactWaves * kRow;            // entries that a workgroup can stage
 constexpr int kMaxSpan = kWordSpan;
+// Scalar registers of gq_compact's kernel, so that eight waves fit on a SIMD (800 for all, handed out in steps of 16, and 16 more to
+// each wave for the trap handler).  With the 87 that help would take, every call is 5 to 12 % slower.  Against no help at all
+// it is equal, but for the longest gradients (300e6: 0.2 % non-zeros 82.9 / 84.8 us, 3 % 89.5 / 94.7).
+constexpr int kCompactScalars = 82;
 
 // A workgroup's span of SPAN codes: cell k of it belongs to wave k mod kCompactWaves.
 template <int SPAN> struct Geometry {
@@ -67,14 +71,20 @@ __device__ __forceinline__ u32x2 load_code_unit(const uint8_t *lv, int64_t t, in
 // No block waits for another block's prefix, so the waits do not chain: a few hundred words are read once or twice per
 // block.
 //
-// Why every wait ends.  One workgroup per span.  Workgroups of a one-dimensional grid are handed to the eight XCDs
-// in turn and each XCD starts its share in increasing order.  Let m be the smallest span not yet finished: every
-// workgroup of m's XCD before m has finished, so m has a free slot and has started; it publishes its count after a
-// bounded amount of work of its own (loads, a count, a block scan) and waits for nothing before that.  A span waits
-// only for counts of earlier spans and for sums of earlier groups, whose writers wait only for counts of their own
-// group: every word m waits for is there, m finishes, and the argument repeats.  The wait is bounded all the same
-// (kPrefixMaxPolls polls of about a microsecond): a workgroup that gives up writes nothing and raises count_out to
-// 2^64 - 1, which no real count reaches.
+// Why every wait ends.  Workgroups of a one-dimensional grid are handed to the eight XCDs in turn and each XCD starts its
+// share in increasing order.  While a grid has the chip to itself, the smallest span not yet finished has therefore a free
+// slot and has started, it publishes its count after a bounded amount of work of its own, and everything that it waits for
+// is there.  Beside other grids that need not hold: two senders on two streams can each fill the slots that the other's
+// oldest span needs.  So a wave of gq_compact that has polled kHelpAfterPolls times, far longer than any wait of a lone grid,
+// counts a missing span itself and publishes the count (help); the span's own workgroup will store the same value.  Each
+// such step puts in one of finitely many words, so every wait ends whatever the order in which workgroups start.
+// gq_quantize_compact has no help: a wave would have to quantise the span, and its registers alone made every call 3 to 15 %
+// slower.  Beside gq_compact and every other kernel it still gets its slots in the end; two of it that share the GPU may
+// wait for each other.  All waits are bounded (kPrefixMaxPolls polls of about a microsecond): a workgroup that gives up
+// writes nothing and raises count_out to 2^64 - 1, which no real count reaches.
+//
+// GQ_MUTE_SPANS = n (a test's build, 0 in the library): spans and groups whose number leaves 1 when divided by n publish
+// nothing, as if they had not started, so that their words come from help alone.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kGroupWords = 64;
 constexpr uint64_t kGroupPublished = 1ull << 40;
@@ -88,7 +98,13 @@ constexpr uint64_t kGroupPublished = 1ull << 40;
 //                         25.6e6: 12.6 / 12.5 / 12.4 / 12.9 / 14.8, 19.6 / 19.6 / 19.9 / 20.7 / 22.5
 constexpr int kWindow = 4;
 constexpr int kWindowMinGroups = 20;
-constexpr int kPrefixMaxPolls = 1 << 21;
+#ifndef GQ_MUTE_SPANS
+#define GQ_MUTE_SPANS 0
+#endif
+constexpr int kMuteSpans = GQ_MUTE_SPANS;
+constexpr int kHelpAfterPolls = kMuteSpans > 0 ? 8 : 4096;                  // a poll takes about a microsecond
+constexpr int kPrefixMaxPolls = kMuteSpans > 0 ? 1 << 13 : 1 << 21;
+__device__ __forceinline__ bool mute(int64_t i) { return kMuteSpans > 0 && i % (kMuteSpans > 0 ? kMuteSpans : 1) == 1; }
 
 // `empty_starts`: the one entry of the table of tile starts of an empty gradient, or nullptr
 __global__ void __launch_bounds__(kBlock) compact_clear_kernel(uint64_t *__restrict__ state, int64_t words, uint64_t *__restrict__ count_out,
@@ -180,6 +196,47 @@ __device__ __forceinline__ void poll_before(const uint64_t *span_words, const ui
     }
 }
 
+struct NoHelp {};
+
+// One missing word of those that `span` waits for, put in by the wave that waits: the count of a span, which `count_of` finds
+// (run by the whole wave, the result is uniform), or, where all counts of a group are there, its sum.  Which missing span is
+// counted depends on the one that waits, so that many waves count different ones.
+template <int SPAN, typename F>
+__device__ __forceinline__ void help(uint64_t *span_words, uint64_t *group_words, int64_t span, const Before &st, F &&count_of)
+{
+    typedef Geometry<SPAN> G;
+    constexpr int kPerWord = G::kPerWord, kGroupSpans = kGroupWords * kPerWord;
+    const int lane = (int)(threadIdx.x & 63u);
+    int64_t group = span / kGroupSpans;
+    if (st.open != 0u) {
+        group += __builtin_ctz(st.open) - kWindow;
+    } else {
+        const bool wanted = st.next_group + lane < st.groups;
+        const uint64_t w = wanted ? state_load(group_words + st.next_group + lane) : kGroupPublished;
+        const uint64_t missing = ballot((w & kGroupPublished) == 0);
+        if (missing == 0) return;
+        group = st.next_group + __builtin_ctzll(missing);
+    }
+    const int64_t first = group * kGroupSpans;
+    const int before = span - first < kGroupSpans ? (int)(span - first) : kGroupSpans;       // spans of the group that count
+    const int mine = before - lane * kPerWord;
+    const uint64_t w = mine > 0 ? state_load(span_words + group * kGroupWords + lane) : 0;
+    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+    const uint64_t low = ballot(mine > 0 && ((kPerWord == 1 ? hi : lo) >> 31) == 0u), high = ballot(kPerWord == 2 && mine > 1 && (hi >> 31) == 0u);
+    if ((low | high) != 0) {
+        const uint64_t any = low | high, later = any >> (span & 63) << (span & 63);
+        const int at = __builtin_ctzll(later != 0 ? later : any);
+        const int64_t other = first + at * kPerWord + ((low >> at & 1) == 0 ? 1 : 0);
+        const uint32_t count = count_of(other);
+        if (lane == 0)
+            __hip_atomic_store(reinterpret_cast<typename G::Field *>(span_words) + other, (typename G::Field)(G::kPublished | count), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    } else if (st.open == 0u) {
+        const uint32_t sum = last_lane(wave_scan(kPerWord == 1 ? lo : (lo & 0x7FFFFFFFu) + (hi & 0x7FFFFFFFu)));
+        if (lane == 0) __hip_atomic_store(group_words + group, kGroupPublished | (uint64_t)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // What the waves of a workgroup share while they turn a span into list entries.
 template <int STAGE> struct SpanShared {
     uint32_t cells[kMaxSpan / kCell];        // non-zeros in every cell of the span
@@ -200,11 +257,12 @@ template <int STAGE> struct SpanShared {
 // the first ends: the slots go to the next workgroups' reads, and the one wave left copies the entries out.  Denser
 // spans wait with all waves, which then rank and copy out 512 codes at a time, each wave in its own part of the
 // staging area and without a barrier.
-template <int SPAN, int W, int STAGE>
+// `count_of` is help's, or NoHelp.
+template <int SPAN, int W, int STAGE, typename F>
 __device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>::kWaveCells], SpanShared<STAGE> &S, int64_t d,
                                           uint64_t *__restrict__ state, int64_t nwords, uint32_t *__restrict__ indices_out,
                                           int8_t *__restrict__ values_out, int64_t capacity, uint64_t *__restrict__ count_out,
-                                          uint32_t *__restrict__ tile_starts_out)
+                                          uint32_t *__restrict__ tile_starts_out, F count_of)
 {
     typedef Geometry<SPAN> G;
     constexpr int kSpanCells = G::kSpanCells, kWaveCells = G::kWaveCells, kGroupSpans = kGroupWords * G::kPerWord;
@@ -217,7 +275,8 @@ __device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>
     const uint32_t cell_start = wave_scan(cell_count) - cell_count;      // entries of the span before cell `lane`
     const uint32_t span_total = (uint32_t)__builtin_amdgcn_readlane((int)cell_start, kSpanCells);
     const uint32_t first_index = (uint32_t)(span * SPAN);
-    if (threadIdx.x == 0)
+    constexpr bool kHelps = !std::is_same<F, NoHelp>::value;
+    if (threadIdx.x == 0 && !(kHelps && mute(span)))
         __hip_atomic_store(reinterpret_cast<typename G::Field *>(span_words) + span, (typename G::Field)(G::kPublished | span_total), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 
@@ -280,20 +339,28 @@ __device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>
     if (wave == 0) {
         Before st = nothing_known<SPAN>(span);
         bool group_sum_out = span % kGroupSpans != kGroupSpans - 1;       // only a group's last span owes one
-        int polls = 0;
-        bool gave_up = false;
-        for (;;) {
+        // one poll; true once everything is there
+        auto poll = [&]() -> bool {
             poll_before<SPAN>(span_words, group_words, span, &st);
             // the group's last span publishes the group's sum as soon as it has it, before it waits on
             if ((st.open >> kWindow & 1u) == 0u && !group_sum_out) {
-                if (lane == 0)
+                if (lane == 0 && !(kHelps && mute(span / kGroupSpans)))
                     __hip_atomic_store(group_words + span / kGroupSpans, kGroupPublished | (uint64_t)(st.in_group + span_total), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
                 group_sum_out = true;
             }
-            if (st.open == 0u && st.next_group >= st.groups) break;
-            if (++polls > kPrefixMaxPolls) { gave_up = true; break; }
-            __builtin_amdgcn_s_sleep(4);
+            return st.open == 0u && st.next_group >= st.groups;
+        };
+        constexpr int kMostPolls = kHelps ? kHelpAfterPolls : kPrefixMaxPolls;
+        int polls = 0;
+        while (!poll() && ++polls <= kMostPolls) __builtin_amdgcn_s_sleep(4);
+        bool gave_up = polls > kMostPolls;
+        if constexpr (kHelps) {
+            if (__builtin_expect(gave_up, 0)) {
+                do help<SPAN>(span_words, group_words, span, st, count_of);
+                while (!poll() && ++polls <= kPrefixMaxPolls);
+                gave_up = polls > kPrefixMaxPolls;
+            }
         }
         const uint64_t before = st.total;
         if (lane == 0) {
@@ -336,7 +403,7 @@ __device__ __forceinline__ void emit_span(const uint32_t (&c)[4 * Geometry<SPAN>
 }
 
 template <int SPAN>
-__global__ void __launch_bounds__(64 * kCompactWaves)
+__global__ void __launch_bounds__(64 * kCompactWaves) __attribute__((amdgpu_num_sgpr(kCompactScalars)))
 compact_onepass_kernel(const uint8_t *__restrict__ lv, int64_t d, uint64_t *__restrict__ state, int64_t nwords,
                        uint32_t *__restrict__ indices_out, int8_t *__restrict__ values_out, int64_t capacity,
                        uint64_t *__restrict__ count_out, uint32_t *__restrict__ tile_starts_out)
@@ -363,7 +430,15 @@ compact_onepass_kernel(const uint8_t *__restrict__ lv, int64_t d, uint64_t *__re
         if (lane == 0) S.cells[b * kCompactWaves + wave] = sum;
     }
     __syncthreads();
-    emit_span<SPAN, 2>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out);
+    emit_span<SPAN, 2>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out, [&](int64_t other) {
+        uint32_t n = 0;
+#pragma unroll 1
+        for (int i = lane; i < SPAN / 8; i += 64) {
+            const u32x2 q = load_code_unit(lv, other * (SPAN / 8) + i, d);
+            n += (uint32_t)(__builtin_popcount(nonzero_bytes(q.x)) + __builtin_popcount(nonzero_bytes(q.y)));
+        }
+        return last_lane(wave_scan(n));
+    });
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -474,7 +549,7 @@ quantize_compact_kernel(const float *__restrict__ x, int64_t d, const float *__r
     if (whole) quantize_cells<SPAN, SCHEME, UNIFORM_HI, HALF, true>(x, d, sc, s == 1, seed, worker, call_base, c, S.cells);
     else quantize_cells<SPAN, SCHEME, UNIFORM_HI, HALF, false>(x, d, sc, s == 1, seed, worker, call_base, c, S.cells);
     __syncthreads();
-    emit_span<SPAN, 1>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out);
+    emit_span<SPAN, 1>(c, S, d, state, nwords, indices_out, values_out, capacity, count_out, tile_starts_out, NoHelp{});
 }
 
 struct SparseLists {

@@ -376,3 +376,64 @@ def test_average_long_launch_equals_pieces(K, pack):
         red1, mean1 = torch.empty(gq.levels_nbytes(n, pack), dtype=torch.uint8, device=DEV), torch.empty(n, device=DEV)
         gq.avg_reduce([c[lo // per:] for c in codes], n, p, lo, norm, red1, mean1)
         assert torch.equal(red[lo // per:lo // per + red1.numel()], red1) and torch.equal(mean[lo:lo + n], mean1)
+
+
+# gq_compact's waits end also where a span that it waits for never comes: in this build every third span, and every third group's
+# sum, is published by nobody but the waves that wait for it.  The lists are the library's, bit for bit; grids with group sums
+# alone and with a window of groups before the own one, short and long spans, ragged ends.
+@pytest.fixture(scope="module")
+def mute():
+    import ctypes
+
+    from paper_2305_18627_amd import build
+    lib = ctypes.CDLL(build.MUTE_LIB)
+    real, f = gq.lib().gq_compact, lib.gq_compact
+    f.restype, f.argtypes = real.restype, real.argtypes
+    return lib
+
+
+@pytest.mark.parametrize("d", [3 * 16_384 + 5, 40 * 16_384, 130 * 16_384 + 77, 700 * 16_384 + 1, 1300 * 32_768 + 77, 4100 * 32_768 + 4099])
+@pytest.mark.parametrize("density", [0.0, 0.001, 0.1, 0.6])
+def test_senders_whose_spans_are_mute(mute, d, density):
+    import ctypes
+    g = torch.Generator(device=DEV).manual_seed(d)
+    lv = torch.randint(1, 256, (d,), generator=g, device=DEV, dtype=torch.int16).to(torch.uint8)
+    lv[torch.rand(d, generator=g, device=DEV) >= density] = 0
+    p = gq.make_params(gq.GQ_LINEAR, 127, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3)
+    want = lists_of(lv, d, p)
+    ws = torch.full((gq.compact_workspace_bytes(d),), 0xFF, dtype=torch.uint8, device=DEV)
+    got = [torch.full_like(want[0], -1), torch.full_like(want[1], 0x5A), torch.full_like(want[2], -1), torch.full_like(want[3], -1)]
+    st = mute.gq_compact(lv.data_ptr(), d, ctypes.byref(p), got[0].data_ptr(), got[1].data_ptr(), d, got[2].data_ptr(), got[3].data_ptr(),
+                         ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert st == gq.GQ_OK
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+# Senders on two streams, each with its own workspace and lists, may share the chip: two of gq_compact, or one of it beside one of
+# gq_quantize_compact.
+@pytest.mark.parametrize("d", [25_600_003, 50_000_001])
+def test_senders_on_two_streams(d):
+    norm = torch.ones(1, device=DEV)
+    p = gq.make_params(gq.GQ_LINEAR, 7, gq.GQ_PACK_I8, gq.GQ_AGG_I32, seed=3)
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    work = []
+    for k in range(2):
+        x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(k), device=DEV).mul_(0.02).clamp_(-1.0, 1.0)
+        lv = torch.empty(d, dtype=torch.uint8, device=DEV)
+        gq.quantize(x, norm, p, 9, 16, lv)
+        want = lists_of(lv, d, p)
+        got = [torch.full_like(want[0], -1), torch.full_like(want[1], 0x5A), torch.full_like(want[2], -1), torch.full_like(want[3], -1)]
+        work.append((x, lv, want, got, torch.empty(gq.compact_workspace_bytes(d), dtype=torch.uint8, device=DEV)))
+    torch.cuda.synchronize()
+    for turn in range(20):
+        for k, ((x, lv, want, got, ws), s) in enumerate(zip(work, side)):
+            if turn % 2 or k:
+                gq.compact(lv, d, p, got[0][:d], got[1][:d], got[2], ws, stream=s, tile_starts_out=got[3])
+            else:
+                gq.quantize_compact(x, norm, p, 9, 16, got[0][:d], got[1][:d], got[2], ws, stream=s, tile_starts_out=got[3])
+    torch.cuda.synchronize()
+    for x, lv, want, got, ws in work:
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
