@@ -66,6 +66,34 @@ def parse():
     return ap.parse_args()
 
 
+def kernel_sources_hash():
+    """sha256 of the sources that the fused kernel is compiled from, without comments and white space."""
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for name in ("quantize.hip", "gq_device.hpp", "gq_host.hpp"):
+        with open(os.path.join(ROOT, "paper_2305_18627_amd", "csrc", name)) as f:
+            h.update("".join(re.sub(r"//[^\n]*", "", f.read()).split()).encode())
+    return h.hexdigest()[:16]
+
+
+def profiled_traffic(path, version):
+    """HBM bytes a launch and the vector ALU's share, profiled offline with rocprofv3 (which cannot run inside this process).
+    The file names the sources of the kernel that was profiled; figures of other sources are not reported."""
+    if not os.path.exists(path):
+        return None, None, None
+    try:
+        with open(path) as f:
+            prof = json.load(f)
+        if prof.get("sources") != kernel_sources_hash():
+            return None, None, ("profiles/ holds counters of other kernel sources (library version %s, commit %s): not reported"
+                                % (prof.get("library_version"), prof.get("git_commit")))
+        return (prof["hbm_bytes_per_launch"], prof["valu_busy_frac"],           # the latter from the SQ counters of the same command
+                "profiled offline with rocprofv3 on the same kernel sources, library version %d (%s)" % (version, prof.get("source")))
+    except Exception as e:
+        return None, None, "traffic figures unreadable: %r" % (e,)
+
+
 def cpu_baseline(xs, nf, scheme, s, seed, sample, bytes_per_coord):
     """The oracle's quantize+sum on the first `sample` coordinates of every worker, split over
     host threads (the C routine runs without the interpreter lock)."""
@@ -355,21 +383,8 @@ def main():
                       "note": "interleaved off/on calls after the timed steps; the headline is the library's default policy"}
 
     traffic = valu_busy = traffic_note = None
-    if args.workload == "c3" and own_shape and os.path.exists(TRAFFIC_FILE):
-        # rocprofv3 cannot run inside this process: the HBM byte counts were profiled offline, and the file says on
-        # which library version; figures of another version are not reported
-        try:
-            prof = json.load(open(TRAFFIC_FILE))
-            if prof.get("library_version") == gq.version():
-                traffic = prof.get("hbm_bytes_per_launch")
-                valu_busy = prof.get("valu_busy_frac")          # from the SQ counters of the same command
-                traffic_note = "profiled offline with rocprofv3 on library version %d (%s)" % (gq.version(), prof.get("source"))
-            else:
-                traffic_note = ("profiles/ holds counters of library version %s, this is %d: not reported"
-                                % (prof.get("library_version"), gq.version()))
-        except Exception as e:
-            traffic = valu_busy = None
-            traffic_note = "traffic figures unreadable: %r" % (e,)
+    if args.workload == "c3" and own_shape:
+        traffic, valu_busy, traffic_note = profiled_traffic(TRAFFIC_FILE, gq.version())
 
     line = {
         "metric": ("fused quantize+aggregate GB/s and % of HBM peak, d=110M K=16 fp32" if args.workload == "c3" and own_shape else

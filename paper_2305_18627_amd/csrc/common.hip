@@ -13,7 +13,7 @@ using namespace gq;
 
 extern "C" {
 
-int gq_version(void) { return 1004; }
+int gq_version(void) { return 1005; }
 
 const char *gq_status_string(gq_status st)
 {
