@@ -144,11 +144,12 @@ def test_quantize_compact_either_side_of_the_long_spans(d, scale):
     check_quantize_compact_equals_two_calls(x, torch.ones(1, device=DEV), p)
 
 
-# From 20 groups of 64 words on, the counts of the four groups before a span's own are read span by span: a grid one span short
-# of that line, one that ends on it with a span of a single code, one beyond it with a ragged group; the first groups of each
-# have fewer than four before them.
+# From 20 groups of 64 words on, the counts of the four groups before a span's own are read span by span.  At these sizes
+# gq_compact has spans of 32768 codes, 64 to a group, and gq_quantize_compact spans of 16384, 128 to a group.  Whole spans one
+# short of the line and a last span of a single code on it: the first two for gq_compact (1279 and 1280 spans), the next two for
+# gq_quantize_compact (2559 and 2560); beyond it a ragged group for both.  The first groups have fewer than four before them.
 @pytest.mark.parametrize("scale", [0.002, 0.3])
-@pytest.mark.parametrize("d", [1279 * 32_768, 1279 * 32_768 + 1, 1300 * 32_768 + 77])
+@pytest.mark.parametrize("d", [1279 * 32_768, 1279 * 32_768 + 1, 2559 * 16_384, 2559 * 16_384 + 1, 1300 * 32_768 + 77])
 def test_senders_either_side_of_the_window_of_groups(d, scale):
     x = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(6), device=DEV).mul_(scale).clamp_(-1.0, 1.0)
     norm = torch.ones(1, device=DEV)
@@ -159,7 +160,7 @@ def test_senders_either_side_of_the_window_of_groups(d, scale):
     check_lists(host(lv).view(np.int8), lists_of(lv, d, p))
 
 
-# The receiver takes a segment of no more than two entries per lane one by one, a longer one four in a row per lane; lists may begin at
+# The receiver takes a segment of no more than two entries per lane both at once, a longer one four in a row per lane; lists may begin at
 # any element of a buffer (indices 4-byte aligned, values anywhere) and end at the last entry of their capacity.
 @pytest.mark.parametrize("K", [1, 2, 5, 8, 16, 33, 64])
 @pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 15, 16, 17, 18, 19, 31, 33, 63, 64, 65, 127, 129, 511, 513, 514, 515, 1023, 1024, 1025, 1026, 2050, 8192])
