@@ -1,9 +1,15 @@
 """The binding's native argument marshalling: what it refuses (no GPU needed) and that every form of an argument that it
 accepts reaches the library alike."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 import paper_2305_18627_amd as gq
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def test_refuses_what_is_not_a_fitting_cuda_tensor():
@@ -33,6 +39,17 @@ def test_refuses_what_is_not_a_fitting_cuda_tensor():
             call(t for t in ())
         with pytest.raises((TypeError, ValueError)):
             call(t for t in (x,))
+
+
+def test_loads_where_torch_has_no_gpu_functions():
+    code = ("import torch\n"
+            "for name in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+            "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+            "import paper_2305_18627_amd as gq\n"
+            "assert gq.version() > 0 and gq.compact_workspace_bytes(1000) > 0\n"
+            "print('loaded')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("loaded"), r.stdout
 
 
 def test_the_marshalling_says_what_it_was_built_for():
