@@ -131,49 +131,40 @@ constexpr int window_min_workers(int bytes) { return bytes <= 4 ? 8 : bytes <= 6
 constexpr double kWindowMinLoads = 2.5e8;         // K * d from which the windows win (measured)
 constexpr int kWindowMaxPolls = 1024;             // polls of about 0.2 us each: the longest period (K = 64, short draws) is 79 us
 
-// The sums and means of a lane's NV vectors, as far as they exist.
-template <int NV, typename A>
-__device__ __forceinline__ void store_sums(const A (&acc)[NV], const int64_t (&v)[NV], const int (&nvalid)[NV], const Scale &sc, float nrm,
-                                           void *agg_out, int agg_fmt, float *deq_out, float deq_div)
+// The sums and means of one vector of which nv > 0 coordinates exist; c = norm / (n * unit), Eq. (1).
+__device__ __forceinline__ void store_sums(i32x4 a, int64_t v, int nv, float c, void *agg_out, int agg_fmt, float *deq_out)
 {
-    const float c = sc.scale != 0.0f ? nrm / deq_div : 0.0f;         // Eq. (1): norm / (n * unit)
-#pragma unroll
-    for (int t = 0; t < NV; t++) {
-        const int nv = nvalid[t];
-        if (nv == 0) break;
-        const i32x4 a = acc[t].get();
-        if (agg_out) {
-            if (agg_fmt == GQ_AGG_I32) {
-                if (nv == 4) {
-                    __builtin_nontemporal_store(a, reinterpret_cast<i32x4 *>(agg_out) + v[t]);
-                } else {
-                    int *o = reinterpret_cast<int *>(agg_out) + (v[t] << 2);
-                    o[0] = a.x;
-                    if (nv > 1) o[1] = a.y;
-                    if (nv > 2) o[2] = a.z;
-                }
+    if (agg_out) {
+        if (agg_fmt == GQ_AGG_I32) {
+            if (nv == 4) {
+                __builtin_nontemporal_store(a, reinterpret_cast<i32x4 *>(agg_out) + v);
             } else {
-                if (nv == 4) {
-                    const i16x4 o = {(short)a.x, (short)a.y, (short)a.z, (short)a.w};
-                    __builtin_nontemporal_store(o, reinterpret_cast<i16x4 *>(agg_out) + v[t]);
-                } else {
-                    short *o = reinterpret_cast<short *>(agg_out) + (v[t] << 2);
-                    o[0] = (short)a.x;
-                    if (nv > 1) o[1] = (short)a.y;
-                    if (nv > 2) o[2] = (short)a.z;
-                }
+                int *o = reinterpret_cast<int *>(agg_out) + (v << 2);
+                o[0] = a.x;
+                if (nv > 1) o[1] = a.y;
+                if (nv > 2) o[2] = a.z;
+            }
+        } else {
+            if (nv == 4) {
+                const i16x4 o = {(short)a.x, (short)a.y, (short)a.z, (short)a.w};
+                __builtin_nontemporal_store(o, reinterpret_cast<i16x4 *>(agg_out) + v);
+            } else {
+                short *o = reinterpret_cast<short *>(agg_out) + (v << 2);
+                o[0] = (short)a.x;
+                if (nv > 1) o[1] = (short)a.y;
+                if (nv > 2) o[2] = (short)a.z;
             }
         }
-        if (deq_out) {
-            if (nv == 4) {
-                const f32x4 o = {(float)a.x * c, (float)a.y * c, (float)a.z * c, (float)a.w * c};
-                __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(deq_out) + v[t]);
-            } else {
-                float *o = deq_out + (v[t] << 2);
-                o[0] = (float)a.x * c;
-                if (nv > 1) o[1] = (float)a.y * c;
-                if (nv > 2) o[2] = (float)a.z * c;
-            }
+    }
+    if (deq_out) {
+        if (nv == 4) {
+            const f32x4 o = {(float)a.x * c, (float)a.y * c, (float)a.z * c, (float)a.w * c};
+            __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(deq_out) + v);
+        } else {
+            float *o = deq_out + (v << 2);
+            o[0] = (float)a.x * c;
+            if (nv > 1) o[1] = (float)a.y * c;
+            if (nv > 2) o[2] = (float)a.z * c;
         }
     }
 }
@@ -306,7 +297,12 @@ quantize_aggregate_kernel(GradPtrsFor<KT> P, typename std::conditional<LEVELS, L
             __builtin_amdgcn_s_sleep(8);
         }
     }
-    store_sums<NV>(acc, v, nvalid, sc, nrm, agg_out, agg_fmt, deq_out, deq_div);
+    const float c = sc.scale != 0.0f ? nrm / deq_div : 0.0f;
+#pragma unroll
+    for (int t = 0; t < NV; t++) {
+        if (nvalid[t] == 0) break;
+        store_sums(acc[t].get(), v[t], nvalid[t], c, agg_out, agg_fmt, deq_out);
+    }
 }
 
 // Short launches.  Their time is latency: a workgroup has code of its own at the ragged end, so that neither the first worker's
@@ -409,7 +405,12 @@ quantize_aggregate_short_block(const GradPtrsFor<KT> &P, const typename std::con
         for (; w < Kc; w++) one_worker(w, fetch(w));
     }
     if (nvalid[0] == 0) return;
-    store_sums<NV>(acc, v, nvalid, sc, nrm, agg_out, agg_fmt, deq_out, deq_div);
+    const float c = sc.scale != 0.0f ? nrm / deq_div : 0.0f;
+#pragma unroll
+    for (int t = 0; t < NV; t++) {
+        if (nvalid[t] == 0) break;
+        store_sums(acc[t].get(), v[t], nvalid[t], c, agg_out, agg_fmt, deq_out);
+    }
 }
 
 template <int SCHEME, int KT, bool LEVELS, bool HALF>
