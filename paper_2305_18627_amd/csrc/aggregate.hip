@@ -181,11 +181,11 @@ __device__ __forceinline__ uint32_t exp_nibble_values(uint32_t n)
     return __builtin_amdgcn_perm(neg, pos, ((n >> 1) & 0x04040404u) | 0x03020100u);
 }
 
-// Workgroups per compute unit (of 16), from kNibLimitFrom coordinates on.  us without a limit / with it: 32-bit sums of 150e6
-// coordinates K = 4 145.4 / 141.8, 8 193.0 / 188.3, 16 290.6 / 283.9, 32 503 / 483, 64 965 / 900; with planes 100e6 K = 8 135.7 / 133.3,
-// 32 427 / 418; 16-bit sums K = 16 243.3 / 233.4, 32 447 / 431 (350e6: 1083 / 1025), 64 881 / 860.  The others lose: planes
-// K = 4 102.0 / 103.6, 16-bit sums K = 8 138.9 / 140.2, with planes 108.5 / 114.3, 32-bit sums of 100e6 K = 1 78 / 88, 2 81 / 86
-// (they write more than they read).
+// Workgroups per compute unit (of 16), from kNibLimitFrom coordinates on.  us without a limit / with it, in turn in one process, 100e6
+// coordinates: 32-bit sums K = 4 97.3 / 95.5, 8 134.6 / 128.5, 16 201.0 / 193.1, 32 358.6 / 340.4, 64 665 / 638; with planes K = 8
+// 148.7 / 142.2, 16 221.2 / 220.2, 32 459 / 455, 64 880 / 873; 16-bit sums K = 16 164.9 / 159.2, 32 315.7 / 303.7, 64 609 / 583.  At 12e6
+// to 25.6e6 coordinates it may lose 2 % (K = 12 22.0 / 22.4, with planes K = 32 104.3 / 106.2).  The others lose: planes K = 4, 16-bit
+// sums K = 8 138.9 / 140.2 (150e6), with planes 108.5 / 114.3, 32-bit sums K = 1 79 / 88, 2 82 / 86 (they write more than they read).
 constexpr int64_t kNibLimitFrom = 10000000;
 static inline int nibble_workgroups(const gq_params *p, int K, int64_t d)
 {

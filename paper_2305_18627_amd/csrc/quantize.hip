@@ -91,11 +91,11 @@ template <> struct Acc<false> {
 };
 
 // Workgroups per compute unit (of 16) where the worker count is known at compile time, the draws are long and no windows
-// separate reads and writes.  us without a limit / with it: K = 4, linear, 40e6 coordinates 129.7 / 121.6, 67e6 211 / 197 (another
-// card: 212 / 204), 110e6 360 / 329; exponential with 16-bit sum and mean 138.8 / 131.8, 232 / 220 (224 / 226.5); K = 8 with the
-// mean, 67e6: 434 / 415 (452 / 447), exponential with a 16-bit sum 418 / 401.5.  K = 8 without the mean is equal, shorter
+// separate reads and writes.  us without a limit / with it, in turn in one process: K = 4 linear, 41e6 coordinates 133.6 / 126, 110e6
+// 361 / 339, exponential with 16-bit sum and mean 142 / 137, 393 / 372, with the sum alone 117.2 / 118.5, 314.1 / 314.6; K = 8 with the
+// mean 281 / 267, 750 / 727, exponential with a 16-bit sum 260 / 250, 711 / 688.  K = 8 without the mean is equal, shorter
 // launches lose (K = 4: 25.6e6 83 / 77 to 90, 6.5e6 21.7 / 23.1), so does K = 16 with its windows (110e6: 1168 / 1394), and
-// short draws are equal.
+// short draws are equal.  Other worker counts run with the loop of run-time length and were not measured with a limit.
 constexpr int64_t kFusedLimitFrom = 40000000;
 template <int SCHEME, int KT, bool LEVELS, bool WINDOWS, bool HALF> static inline int fused_workgroups(int64_t coords, bool mean)
 {
@@ -571,6 +571,9 @@ quantize_kernel(const float *__restrict__ x, void *__restrict__ lv, uint32_t *__
 //   linear  int8 757 / 754.5, 351 / 346;  int4 693 / 681, 316 / 310;  8 bits + planes 819 / 814, 356 / 346;  4 bits + planes 706 / 689, 316 / 333
 //   exponential, 8 bits + planes  844 / 825, 358 / 381;  its other formats only lose (with 14: int4 684 / 676, 334 / 346;  4 bits + planes 794 / 790,
 //   347 / 358;  int8 equal, 349 / 359)
+// Again, in turn in one process: four calls of 110e6 between norm and sum, eight of 67e6, four of 110e6 in a loop: 4 bits + planes
+// 729 / 705, 838 / 818, 326 / 342;  exponential, 8 bits + planes 855 / 840, 949 / 932, 361 / 383.  These two formats pay 5 to 6 % where
+// a caller only encodes and gain 2 to 3 % where it takes the norm and the sum as well, which is what the codes are for.
 constexpr int64_t kQuantLimitFrom = 50000000;
 static inline int quantize_workgroups(const gq_params *p, int64_t d)
 {

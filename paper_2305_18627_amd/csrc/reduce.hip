@@ -545,7 +545,8 @@ avg_reduce_kernel(CodePtrs Lv, int K, int64_t d, uint64_t seed, uint64_t call_ba
 // Threads per workgroup of the averaging kernel, and workgroups per compute unit (0: as many as fit).  Trees of up to eight leaves
 // are as fast or faster in workgroups of 256 (110e6 x 4: 150 us, 155 in 128), larger ones in 128 (12e6 x 16: 40.5, 42.8 in 256; 50e6
 // x 16 in nibbles: 120, 124.5), except for long launches of 16 and more workers' bytes, which are bound by memory and
-// run best with few waves: 110e6 x 16 368 us in 128, 354 in 256 and five a unit; 50e6 x 32 315.5 and 302; 25.6e6 x 16 85.4 and 84.3.
+// run best with few waves: in 256, in turn in one process, without a limit and with five a unit 110e6 x 16 386 and 367 us, 50e6 x 16 173
+// and 168, 26e6 x 16 90 and 87 (in 128 without a limit 110e6 x 16 lies 4 % above the latter, 50e6 x 32 and 25.6e6 x 16 4 and 1 %).
 constexpr int64_t kAverageLimitFrom = 25000000;
 static inline int average_threads(int K, int64_t d, bool nibbles, int *per_cu)
 {
