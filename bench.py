@@ -102,7 +102,7 @@ def cpu_baseline(xs, nf, scheme, s, seed, sample, bytes_per_coord):
     d = xs[0].numel()
     sample = min(sample, d)
     host = [x[:sample].cpu().numpy() for x in xs]
-    # every host core this job may use: a GPU machine gives a one-GPU job a share of 16 cores whatever
+    # every host core this job may use: a one-GPU job may have a share of 16 cores whatever
     # os.cpu_count() shows there (OMP_NUM_THREADS carries that share)
     share = int(os.environ.get("OMP_NUM_THREADS", "0") or 0)
     threads = max(1, min(os.cpu_count() or 1, share if share > 0 else 16))
