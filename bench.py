@@ -11,7 +11,7 @@ inside them.  One JSON line is printed:
              (4K bytes read + 4 bytes written per output coordinate, divided by the call's mean
              duration inside the timed steps), inputs resident in HBM
   roofline   the same kernel against MI355X's 8 TB/s HBM peak; `traffic` is the HBM byte count per
-             launch from rocprofv3 FETCH_SIZE/WRITE_SIZE counters (read from profiles/, null if absent)
+             launch from rocprofv3 FETCH_SIZE/WRITE_SIZE counters (read from profiles/, null if absent or of other kernel sources)
   step_*     the whole step: ms, algorithmic bytes, GB/s
   cpu_baseline  the CPU oracle (as it stands) on a bounded sample of the same buffers
 """
